@@ -335,9 +335,8 @@ static size_t block_ws(const bc_block_desc& d, void* base, BlockBufs* bb, float*
 static SkinnyArgs skinny1(const void* W, const void* b, int N, int K, int B, const float* in, float* out,
                           int act_in, int act_out) {
     SkinnyArgs a;
-    std::memset(&a, 0, sizeof a);
-    a.W[0] = W; a.bias[0] = b;
-    a.nseg = 1; a.Nseg = N; a.K = K; a.B = B;
+    a.W = W; a.bias = b;
+    a.N = N; a.K = K; a.B = B;
     a.in = in; a.ld_in = K; a.out = out; a.ld_out = N;
     a.act_in = act_in; a.act_out = act_out;
     return a;

@@ -13,19 +13,16 @@ constexpr int kMaxSeg = 64;
 int launch_ln_mod(int in_dt, const void* x, int64_t rows, int D, const float* shift, const float* scale,
                   int64_t ld_mod, int rows_per_sample, int out_dt, void* h, hipStream_t s);
 
-// Skinny linear for per-sample vectors (B <= 64 rows), weights `dt`:
-//   out[b, seg*Nseg + n] = act_out(sum_k act_in(in[b, k]) W_seg[n, k] + bias_seg[n])
-// for each of `nseg` segments with their own W/bias; act: 0 none, 1 SiLU.
-// `addend` (fp32 [B, nseg*Nseg] or NULL) is added after act_out.
+// Skinny linear for per-sample vectors (B <= 64 rows), weights `dt` [N, K]:
+//   out[b, n] = act_out(sum_k act_in(in[b, k]) W[n, k] + bias[n]);
+// act: 0 none, 1 SiLU.
 struct SkinnyArgs {
-    const void* W[kMaxSeg];
-    const void* bias[kMaxSeg];
-    int nseg, Nseg, K, B;
+    const void *W, *bias;
+    int N, K, B;
     const float* in;
     int64_t ld_in;
     float* out;
     int64_t ld_out;
-    const float* addend;
     int act_in, act_out;
 };
 int launch_skinny(int dt, const SkinnyArgs& a, hipStream_t s);

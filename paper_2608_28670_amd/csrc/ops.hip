@@ -174,127 +174,151 @@ int launch_ln_mod(int in_dt, const void* x, int64_t rows, int D, const float* sh
 }
 
 // ---------------------------------------------------------------------------
-// Skinny linear on MFMA: a 16 x 16 output tile per wave (16 samples x 16
-// output features); act(in) is staged in LDS in the weight dtype, the weights
-// stream straight from HBM into the B operand.
+// Skinny linear on MFMA.  A workgroup of 8 waves owns 16 rows of the batch
+// (grid.y) and 16 TN output features; the waves deal the k-chunks among
+// themselves (wave w takes chunks w, w + 8, ...) and meet in LDS once at the
+// end, in a fixed order.  What bounds it is the one read of the weights, so
+// they go straight from memory to the MFMA's B operand, 16 bytes a lane, with
+// U chunks of every tile issued before the first is used; splitting k over the
+// waves is what puts enough of them in flight (a workgroup per 256 features
+// with the whole of k behind two barriers left 27 to 72 workgroups: 33 us for
+// the 16 MB of DiT-XL/2's modulation, 79 us for the video model's 113 MB).
+// The activation is applied as the A operand is loaded: each wave needs only
+// its own chunks of it.
 // ---------------------------------------------------------------------------
 template <typename T> struct SkMma;
 template <> struct SkMma<bf16> {
-    static constexpr int E = 8, KI = 32, KC = 1024;
-    typedef bf16x8 frag;
-    __device__ static f32x4 mma(const frag& a, const frag& b, const f32x4& c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    static constexpr int E = 8, KI = 32;      // elements per lane, k per chunk
+    __device__ static f32x4 mma(const u32x4& a, const u32x4& b, const f32x4& c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
     }
-    __device__ static frag load(const bf16* p) { return __builtin_bit_cast(frag, *reinterpret_cast<const u32x4*>(p)); }
-    __device__ static frag zero() { return __builtin_bit_cast(frag, u32x4{0, 0, 0, 0}); }
+    __device__ static u32x4 pack(const float* v) {
+        bf16x8 q;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) q[i] = (bf16)v[i];
+        return __builtin_bit_cast(u32x4, q);
+    }
 };
+// fp32: lane group g of a chunk holds k = 4 g .. 4 g + 3, and instruction i
+// takes element i of every lane; both operands permute k alike.
 template <> struct SkMma<float> {
-    static constexpr int E = 1, KI = 4, KC = 512;
-    typedef float frag;
-    __device__ static f32x4 mma(frag a, frag b, const f32x4& c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    static constexpr int E = 4, KI = 16;
+    __device__ static f32x4 mma(const u32x4& a, const u32x4& b, f32x4 c) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[i]), __uint_as_float(b[i]), c, 0, 0, 0);
+        return c;
     }
-    __device__ static frag load(const float* p) { return *p; }
-    __device__ static frag zero() { return 0.f; }
+    __device__ static u32x4 pack(const float* v) {
+        return u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+    }
 };
 
-constexpr int kSkTiles = 4;   // 16-column tiles per wave
-constexpr int kSkBatch = 8;   // k-steps of weight loads issued together
+constexpr int kSkWaves = 8;
+constexpr int kSkBatch = 4;   // chunks of weight loads issued together
 
-template <typename T_>
-__global__ __launch_bounds__(256) void skinny_kernel(SkinnyArgs a) {
+template <typename T_, int TN>
+__global__ __launch_bounds__(64 * kSkWaves) void skinny_kernel(SkinnyArgs a) {
     typedef elem_t<T_> T;
     typedef SkMma<T> MM;
-    constexpr int KC = MM::KC;
-    constexpr int PAD = 16 / (int)sizeof(T);
-    __shared__ __attribute__((aligned(16))) T sIn[16][KC + PAD];
+    constexpr int E = MM::E, U = kSkBatch;
+    __shared__ __attribute__((aligned(16))) f32x4 red[kSkWaves][TN][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int Ntot = a.nseg * a.Nseg;
-    const int nbase = blockIdx.x * (4 * kSkTiles * 16) + wave * kSkTiles * 16;
-    const int r16 = lane & 15, kg = (lane >> 4) * MM::E;
-
-    for (int b0 = 0; b0 < a.B; b0 += 16) {
-        f32x4 acc[kSkTiles];
+    const int r16 = lane & 15, kg = (lane >> 4) * E;
+    const int n0 = blockIdx.x * 16 * TN, b0 = blockIdx.y * 16;
+    const T* W = static_cast<const T*>(a.W);
+    const T* wr[TN];
 #pragma unroll
-        for (int t = 0; t < kSkTiles; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int kc0 = 0; kc0 < a.K; kc0 += KC) {
-            const int kn = min(KC, a.K - kc0);
-            __syncthreads();
-            for (int i = tid; i < 16 * KC; i += 256) {
-                const int bb = i / KC, k = i % KC;
-                float v = 0.f;
-                if (b0 + bb < a.B && k < kn) {
-                    v = a.in[(int64_t)(b0 + bb) * a.ld_in + kc0 + k];
-                    if (a.act_in == 1) v = silu(v);
-                }
-                sIn[bb][k] = (T)v;
-            }
-            __syncthreads();
-            // Weight rows of this wave's tiles (NULL past the end).
-            const T* wr[kSkTiles];
+    for (int t = 0; t < TN; ++t) wr[t] = W + (int64_t)min(n0 + 16 * t + r16, a.N - 1) * a.K;
+    const bool row_ok = b0 + r16 < a.B;
+    const float* in = a.in + (int64_t)min(b0 + r16, a.B - 1) * a.ld_in;
+    const bool vec = reinterpret_cast<uintptr_t>(a.in) % 16 == 0 && a.ld_in % 4 == 0;   // the caller's vectors may be unaligned
+    f32x4 acc[TN];
 #pragma unroll
-            for (int t = 0; t < kSkTiles; ++t) {
-                const int ncol = nbase + t * 16;
-                wr[t] = nullptr;
-                if (ncol < Ntot) {
-                    const int seg = ncol / a.Nseg;
-                    const int nloc = ncol - seg * a.Nseg + r16;
-                    wr[t] = static_cast<const T*>(a.W[seg]) + (int64_t)nloc * a.K + kc0;
-                }
-            }
-            // kSkBatch k-steps of every tile's weights in flight before the MFMAs.
-            for (int k0 = 0; k0 < kn; k0 += kSkBatch * MM::KI) {
-                typename MM::frag wf[kSkTiles][kSkBatch];
+    for (int t = 0; t < TN; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int nch = (a.K + MM::KI - 1) / MM::KI;
+    for (int c0 = wave; c0 < nch; c0 += kSkWaves * U) {
+        u32x4 wf[U][TN];
+        float v[U][E];
 #pragma unroll
-                for (int t = 0; t < kSkTiles; ++t)
+        for (int u = 0; u < U; ++u) {
+            const int k = (c0 + u * kSkWaves) * MM::KI + kg;     // K % E == 0: a lane's piece is wholly in or out
+            const bool ok = k < a.K;
 #pragma unroll
-                    for (int u = 0; u < kSkBatch; ++u) {
-                        const int k = k0 + u * MM::KI + kg;
-                        wf[t][u] = (wr[t] && k < kn) ? MM::load(wr[t] + k) : MM::zero();
+            for (int t = 0; t < TN; ++t)
+                wf[u][t] = ok ? *reinterpret_cast<const u32x4*>(wr[t] + k) : u32x4{0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = (c0 + u * kSkWaves) * MM::KI + kg;
+            if (row_ok && k < a.K) {
+                if (vec) {
+#pragma unroll
+                    for (int i = 0; i < E; i += 4) {
+                        const f32x4 x = *reinterpret_cast<const f32x4*>(in + k + i);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[u][i + e] = x[e];
                     }
+                } else {
 #pragma unroll
-                for (int u = 0; u < kSkBatch; ++u) {
-                    const int k = k0 + u * MM::KI;
-                    if (k >= kn) break;
-                    const typename MM::frag af = MM::load(&sIn[r16][k + kg]);
-#pragma unroll
-                    for (int t = 0; t < kSkTiles; ++t) acc[t] = MM::mma(af, wf[t][u], acc[t]);
+                    for (int i = 0; i < E; ++i) v[u][i] = in[k + i];
                 }
+                if (a.act_in == 1) {
+#pragma unroll
+                    for (int i = 0; i < E; ++i) v[u][i] = silu(v[u][i]);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < E; ++i) v[u][i] = 0.f;
             }
         }
 #pragma unroll
-        for (int t = 0; t < kSkTiles; ++t) {
-            const int ncol = nbase + t * 16;
-            if (ncol >= Ntot) break;
-            const int seg = ncol / a.Nseg;
-            const int nloc = ncol - seg * a.Nseg + r16;
-            const float bv = a.bias[seg] ? ld(static_cast<const T*>(a.bias[seg]) + nloc) : 0.f;
+        for (int u = 0; u < U; ++u) {
+            const u32x4 af = MM::pack(v[u]);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int bb = b0 + 4 * (lane >> 4) + r;
-                if (bb >= a.B) continue;
-                float v = acc[t][r] + bv;
-                if (a.act_out == 1) v = silu(v);
-                const int64_t o = (int64_t)bb * a.ld_out + ncol + r16;
-                if (a.addend) v += a.addend[o];
-                a.out[o] = v;
-            }
+            for (int t = 0; t < TN; ++t) acc[t] = MM::mma(af, wf[u][t], acc[t]);
         }
+    }
+#pragma unroll
+    for (int t = 0; t < TN; ++t) red[wave][t][lane] = acc[t];
+    __syncthreads();
+    // Wave t finishes tile t: lane l holds rows 4 (l / 16) .. + 3 of column l % 16.
+    if (wave >= TN) return;
+    f32x4 sum = red[0][wave][lane];
+#pragma unroll
+    for (int w = 1; w < kSkWaves; ++w) sum += red[w][wave][lane];
+    const int n = n0 + 16 * wave + r16;
+    if (n >= a.N) return;
+    const float bv = a.bias ? ld(static_cast<const T*>(a.bias) + n) : 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int b = b0 + 4 * (lane >> 4) + r;
+        if (b >= a.B) continue;
+        float v = sum[r] + bv;
+        if (a.act_out == 1) v = silu(v);
+        a.out[(int64_t)b * a.ld_out + n] = v;
     }
 }
 
+template <typename T_>
+static void run_skinny(const SkinnyArgs& a, hipStream_t s) {
+    // Features per workgroup: as many tiles (up to four, so that the
+    // activation is worked out fewer times) as leave a workgroup for every CU.
+    const unsigned tiles = (unsigned)((a.N + 15) / 16), rows = (unsigned)((a.B + 15) / 16);
+    const dim3 block(64 * kSkWaves);
+    if (tiles * rows >= 4 * 256) skinny_kernel<T_, 4><<<dim3((tiles + 3) / 4, rows), block, 0, s>>>(a);
+    else if (tiles * rows >= 2 * 256) skinny_kernel<T_, 2><<<dim3((tiles + 1) / 2, rows), block, 0, s>>>(a);
+    else skinny_kernel<T_, 1><<<dim3(tiles, rows), block, 0, s>>>(a);
+}
+
 int launch_skinny(int dt, const SkinnyArgs& a, hipStream_t s) {
-    if (a.B <= 0 || a.nseg <= 0) return BC_OK;
+    if (a.B <= 0) return BC_OK;
     if (a.B > 64) return fail(BC_ERR_UNSUPPORTED, "conditioning batch %d > 64", a.B);
-    if (a.nseg > kMaxSeg || a.Nseg % 16 || a.K % (dt == BC_BF16 ? 8 : 4))
-        return fail(BC_ERR_UNSUPPORTED, "skinny linear segments=%d N=%d K=%d", a.nseg, a.Nseg, a.K);
-    for (int i = 0; i < a.nseg; ++i)
-        if (!a.W[i] || reinterpret_cast<uintptr_t>(a.W[i]) % 16)
-            return fail(BC_ERR_INVALID_ARG, "skinny linear weight %d missing or misaligned", i);
-    const int Ntot = a.nseg * a.Nseg;
-    const unsigned grid = (unsigned)((Ntot + 4 * kSkTiles * 16 - 1) / (4 * kSkTiles * 16));
-    if (dt == BC_BF16) skinny_kernel<bf16_tag><<<grid, 256, 0, s>>>(a);
-    else skinny_kernel<float><<<grid, 256, 0, s>>>(a);
+    if (a.N % 16 || a.K % (dt == BC_BF16 ? 8 : 4)) return fail(BC_ERR_UNSUPPORTED, "skinny linear N=%d K=%d", a.N, a.K);
+    if (!a.W || reinterpret_cast<uintptr_t>(a.W) % 16)
+        return fail(BC_ERR_INVALID_ARG, "skinny linear weight missing or misaligned");
+    if (dt == BC_BF16) run_skinny<bf16_tag>(a, s);
+    else run_skinny<float>(a, s);
     return check_launch("skinny linear");
 }
 

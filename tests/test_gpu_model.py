@@ -498,3 +498,42 @@ def test_sample_cfg_rejects_unconditional_model(bclib):
     with pytest.raises(bclib.BCError) as e:
         dm.sample_cfg(x, bary.make_mask(cfg.steps, cfg.interval), torch.zeros(2, dtype=torch.int64, device=DEV), 1.5)
     assert e.value.code == bclib.ERR_UNSUPPORTED
+
+
+# The modulation linear alone: with w_o = w_fc2 = 0 and b_o = b_fc2 = 1 a DiT
+# block adds gate1 + gate2, columns 2D.. and 5D.. of SiLU(c) W_mod^T + b_mod.
+# Widths whose k is a whole number of the MFMA's chunks or not (80, 112: a
+# partial one), fewer chunks than waves (64) and several per wave (1152); one,
+# two and four column tiles per workgroup (N = 6 D); one sample, a full and a
+# ragged group of 16; c at any 4-byte alignment.
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("B,heads,hd,off", [(1, 2, 32, 0), (16, 16, 72, 0), (17, 2, 72, 1), (3, 7, 64, 0), (33, 30, 64, 3),
+                                            (2, 3, 32, 1), (1, 46, 64, 0)])
+def test_modulation_linear(bclib, dt, B, heads, hd, off):
+    if dt == "f32" and hd > 64:
+        pytest.skip("fp32 blocks take head dims up to 64")
+    D, F, T = heads * hd, 64, 2
+    tdt = torch.bfloat16 if dt == "bf16" else torch.float32
+    g = torch.Generator(device=DEV)
+    g.manual_seed(D + B)
+
+    def rnd(*s, scale=1.0):
+        return torch.empty(s, device=DEV).normal_(0.0, scale, generator=g)
+
+    w = {"w_mod": rnd(6 * D, D, scale=0.05), "b_mod": rnd(6 * D, scale=0.1), "w_qkv": rnd(3 * D, D, scale=0.02),
+         "b_qkv": rnd(3 * D), "w_o": torch.zeros(D, D, device=DEV), "b_o": torch.ones(D, device=DEV),
+         "w_fc1": rnd(F, D, scale=0.02), "b_fc1": rnd(F), "w_fc2": torch.zeros(D, F, device=DEV),
+         "b_fc2": torch.ones(D, device=DEV)}
+    w = {k: v.to(tdt) for k, v in w.items()}
+    c = rnd(B * D + off)[off:].view(B, D)
+    x = torch.zeros(B, T, D, device=DEV)
+    desc = bclib.block_desc(bclib.BLOCK_DIT, B, T, D, heads, hd, F, bclib.BF16 if dt == "bf16" else bclib.F32)
+    ws = torch.empty(bclib.block_workspace_size(desc), dtype=torch.uint8, device=DEV)
+    bclib.dit_block_forward(desc, bclib.block_weights(w), x, c, ws)
+    torch.cuda.synchronize()
+    a = torch.nn.functional.silu(c.double())
+    mod = a @ w["w_mod"].double().T.contiguous() + w["b_mod"].double()
+    want = (mod[:, 2 * D:3 * D] + mod[:, 5 * D:])[:, None, :].expand(B, T, D)
+    err = float((x.double() - want).norm() / want.norm())
+    # bf16: the activation is rounded once (2^-9 relative each, averaged over D terms); fp32: sums of D terms
+    assert err <= (3e-3 if dt == "bf16" else 2e-6), err
