@@ -866,6 +866,219 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
     launch_k(gemm_dma_kernel<EPI, BM, BN, WAVES_M, WAVES_N, STAGES, SW>, dim3(tiles), dim3(64 * WAVES_M * WAVES_N), s, g);
 }
 
+// ---------------------------------------------------------------------------
+// Small grids: K split over the waves of a workgroup.
+//
+// With few rows the tiles above leave most CUs idle and walk all of K as one
+// serial chain of loads, barrier and MFMAs (M = 256, N = 1152, K = 4608: 16
+// workgroups, 72 steps, 46 us).  Here a tile is small, and each of the WK waves
+// accumulates all of it over k-steps of its own (wave w takes steps w, w + WK,
+// ...; a step is 128 bytes of every operand row), loaded straight into a ring
+// of S stages that only this wave uses: the loads of the waves keep each other
+// company, and no barrier stops them until the partial tiles meet in LDS, in a
+// fixed order, for the epilogue.  What bounds it is what a CU's loads deliver,
+// about 64 GB/s, so the time is close to (rounds of workgroups) (BM + BN) K
+// bytes over that: 10.6 us for the shape above.  (Fragments loaded from global
+// memory straight into registers, without the trip through LDS, ran at a third
+// of that: the 16 lanes of a fragment row fetch from 16 rows, 16 bytes each.)
+// Any N and alignment of the outputs (vec: 4-column accesses are possible).
+// ---------------------------------------------------------------------------
+// One wave-wide direct-to-LDS load from a wave-uniform base plus a 32-bit byte
+// offset per lane.
+__device__ __forceinline__ void dma16s(const void* base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds) : "memory", "m0");
+}
+
+template <typename T> struct KsMma;
+template <> struct KsMma<bf16> {
+    __device__ static __forceinline__ f32x4 mma(const u32x4& w, const u32x4& a, const f32x4& c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, a), c, 0, 0, 0);
+    }
+};
+// fp32: instruction i takes element i of every lane, k = 4 (l / 16) + i.
+template <> struct KsMma<float> {
+    __device__ static __forceinline__ f32x4 mma(const u32x4& w, const u32x4& a, f32x4 c) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w[i]), __uint_as_float(a[i]), c, 0, 0, 0);
+        return c;
+    }
+};
+
+// The epilogue of four consecutive columns of one row (see GemmEpi); columns
+// past N are dropped.
+template <typename T, int EPI>
+__device__ __forceinline__ void finish4(const GemmArgs& g, int row, int col, const f32x4& acc, bool vec) {
+    const GemmEpi& e = g.e;
+    const T* bias = static_cast<const T*>(e.bias);
+    if constexpr (EPI == BC_EPI_GATE_RES) {
+        const int b = row / e.seg, sidx = row - b * e.seg;
+        if (sidx >= e.keep) return;
+        const int64_t o = (int64_t)(b * e.keep + sidx) * e.ldo + col;
+        const float* res = e.res + (int64_t)row * e.ldr + col;
+        const float* gate = e.gate ? e.gate + (int64_t)(row / e.rows_per_gate) * e.ldg + col : nullptr;
+        float v[4];
+        if (vec) {
+            const f32x4 rv = *reinterpret_cast<const f32x4*>(res);
+            const f32x4 gv = gate ? *reinterpret_cast<const f32x4*>(gate) : f32x4{1.f, 1.f, 1.f, 1.f};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = rv[r] + gv[r] * (acc[r] + (bias ? ld(bias + col + r) : 0.f));
+            if (e.out_f32) st4(static_cast<float*>(e.out) + o, v);
+            else if constexpr (sizeof(T) == 2) st4(static_cast<bf16*>(e.out) + o, v);
+            return;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (col + r >= g.N) break;
+            const float y = res[r] + (gate ? gate[r] : 1.f) * (acc[r] + (bias ? ld(bias + col + r) : 0.f));
+            if (e.out_f32) static_cast<float*>(e.out)[o + r] = y;
+            else st(static_cast<T*>(e.out) + o + r, y);
+        }
+    } else {
+        float v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            v[r] = acc[r] + (bias && col + r < g.N ? ld(bias + col + r) : 0.f);
+            if (col + r < e.q_scale_to) v[r] *= e.q_scale;
+            if (col + r >= e.gelu_from) v[r] = gelu_tanh(v[r]);
+        }
+        if (vec) {     // the boundaries are multiples of 4: all four columns go one way
+            if (col >= e.split) st4(static_cast<T*>(e.out2) + (int64_t)row * e.ldo2 + (col - e.split + e.off2), v);
+            else if (e.out_f32) st4(static_cast<float*>(e.out) + (int64_t)row * e.ldo + col, v);
+            else st4(static_cast<T*>(e.out) + (int64_t)row * e.ldo + col, v);
+            return;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int c = col + r;
+            if (c >= g.N) break;
+            if (c >= e.split) st(static_cast<T*>(e.out2) + (int64_t)row * e.ldo2 + (c - e.split + e.off2), v[r]);
+            else if (e.out_f32) static_cast<float*>(e.out)[(int64_t)row * e.ldo + c] = v[r];
+            else st(static_cast<T*>(e.out) + (int64_t)row * e.ldo + c, v[r]);
+        }
+    }
+}
+
+template <typename T_, int EPI, int TM, int TN, int WK, int S>
+__global__ __launch_bounds__(64 * WK) void gemm_ksplit_kernel(GemmArgs g, int vec) {
+    typedef elem_t<T_> T;
+    typedef KsMma<T> MM;
+    constexpr int BM = 16 * TM, BN = 16 * TN, PITCH = BN + 4;
+    constexpr int BK = 128 / (int)sizeof(T);               // k per step: 128 bytes of every row
+    constexpr int Q = (BM + BN) / 8;                       // wave-wide loads per step
+    constexpr int STAGE = (BM + BN) * 128, RING = S * STAGE;
+    // Partial tiles held in LDS at once: all of them, or half (a quarter) of them.
+    constexpr int SLOT = BM * PITCH;
+    constexpr int NS = WK * SLOT * 4 <= WK * RING ? WK : WK * SLOT * 2 <= WK * RING ? WK / 2 : WK / 4;
+    static_assert(NS >= 1 && NS * SLOT * 4 <= WK * RING && WK * RING <= 160 * 1024, "LDS");
+    __shared__ __attribute__((aligned(1024))) char sm[WK * RING];
+    typedef __attribute__((address_space(3))) const char lds_char;
+    typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, grp = lane >> 4;
+    // Row tiles fastest: the workgroups that share a column tile's weights are neighbours on one XCD.
+    const int tiles_m = (g.M + BM - 1) / BM;
+    const int pid = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int bm = pid % tiles_m * BM, bn = pid / tiles_m * BN;
+    const char* baseA = reinterpret_cast<const char*>(static_cast<const T*>(g.A) + (int64_t)bm * g.lda);
+    const char* baseW = reinterpret_cast<const char*>(static_cast<const T*>(g.W) + (int64_t)bn * g.ldw);
+    uint32_t voff[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int r = 8 * q + (lane >> 3);
+        const uint32_t ch = ((lane & 7) ^ ((r >> 1) & 7)) * 16;
+        voff[q] = r < BM ? (uint32_t)(min(bm + r, g.M - 1) - bm) * (uint32_t)(g.lda * sizeof(T)) + ch
+                         : (uint32_t)(min(bn + r - BM, g.N - 1) - bn) * (uint32_t)(g.ldw * sizeof(T)) + ch;
+    }
+    const uint32_t ring = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_char*)sm + wave * RING);
+    // Step i of this wave is k-step wave + WK i, in stage i % S of its ring.
+    const int nk = g.K / BK;
+    const int n = nk > wave ? (nk - wave + WK - 1) / WK : 0;
+    auto issue = [&](int i, int stage) __attribute__((always_inline)) {
+        const int64_t k = (int64_t)(wave + WK * i) * 128;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) dma16s((8 * q < BM ? baseA : baseW) + k, voff[q], ring + stage * STAGE + q * 1024);
+    };
+    lds_char* frag[2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+        frag[kk] = (lds_char*)sm + wave * RING + r16 * 128 + ((kk * 4 + grp) ^ ((r16 >> 1) & 7)) * 16;
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int p = 0; p < S; ++p)
+        if (p < n) issue(p, p);
+    int stage = 0;
+    for (int i = 0; i < n; ++i) {
+        wait_groups<Q, 0, S - 1>(min(S - 1, n - 1 - i));       // step i has landed; later ones may be on their way
+        asm volatile("" ::: "memory");
+        u32x4 fa[2][TM], fw[2][TN];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fw[kk][j] = *(lds_u32x4*)(frag[kk] + stage * STAGE + (BM + 16 * j) * 128);
+#pragma unroll
+            for (int m = 0; m < TM; ++m) fa[kk][m] = *(lds_u32x4*)(frag[kk] + stage * STAGE + 16 * m * 128);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // read before the stage is filled again
+        if (i + S < n) issue(i + S, stage);
+        stage = stage + 1 == S ? 0 : stage + 1;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int m = 0; m < TM; ++m)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[m][j] = MM::mma(fw[kk][j], fa[kk][m], acc[m][j]);
+    }
+    __syncthreads();      // the partial tiles take the rings' place
+    float* red = reinterpret_cast<float*>(sm);
+    // Partial tiles to LDS: the last NS waves store, the groups of NS before them add.
+#pragma unroll
+    for (int r = WK / NS - 1; r >= 0; --r) {
+        if (wave / NS == r) {
+            float* slot = red + (wave % NS) * SLOT;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    f32x4* d = reinterpret_cast<f32x4*>(slot + (16 * i + r16) * PITCH + 16 * j + 4 * grp);
+                    *d = r == WK / NS - 1 ? acc[i][j] : *d + acc[i][j];
+                }
+        }
+        __syncthreads();
+    }
+    constexpr int C4 = BN / 4;
+    for (int q = tid; q < BM * C4; q += 64 * WK) {
+        const int lr = q / C4, lc = (q - lr * C4) * 4;
+        const int row = bm + lr, col = bn + lc;
+        if (row >= g.M || col >= g.N) continue;
+        f32x4 sum = *reinterpret_cast<const f32x4*>(red + lr * PITCH + lc);
+#pragma unroll
+        for (int w = 1; w < NS; ++w) sum += *reinterpret_cast<const f32x4*>(red + w * SLOT + lr * PITCH + lc);
+        finish4<T, EPI>(g, row, col, sum, vec != 0);
+    }
+}
+
+template <typename T, int EPI, int TM, int TN, int WK, int S>
+static void launch_ksplit(const GemmArgs& g, bool vec, hipStream_t s) {
+    const unsigned tiles = (unsigned)(((g.M + 16 * TM - 1) / (16 * TM)) * ((g.N + 16 * TN - 1) / (16 * TN)));
+    launch_k(gemm_ksplit_kernel<tag_t<T>, EPI, TM, TN, WK, S>, dim3(tiles), dim3(64 * WK), s, g, vec ? 1 : 0);
+}
+
+// Whether every column index, stride and boundary of the epilogue is a
+// multiple of 4 elements and its pointers allow accesses of that width.
+static bool vec4_ok(const GemmArgs& g, int epi) {
+    const GemmEpi& e = g.e;
+    auto al = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
+    if (g.N % 4 || e.ldo % 4 || !al(e.out)) return false;
+    if (epi == BC_EPI_GATE_RES) return e.ldr % 4 == 0 && al(e.res) && (!e.gate || (e.ldg % 4 == 0 && al(e.gate)));
+    return e.split >= g.N || (e.split % 4 == 0 && e.off2 % 4 == 0 && e.ldo2 % 4 == 0 && al(e.out2));
+}
+
 template <typename T, int EPI, int BM, int BN, int WAVES_M, int WAVES_N>
 static void launch_tile(const GemmArgs& g, hipStream_t s) {
     const unsigned tiles = (unsigned)(((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN));
@@ -906,10 +1119,54 @@ static bool wide_ok(const GemmArgs& g, int epi) {
 //   * otherwise 128 x 128 (8 waves of 32 x 64, two workgroups per CU).
 // Other bf16 operands take the direct-to-LDS kernel with the scalar
 // epilogue, or the register-staged kernel; fp32 the register-staged kernel.
+// Before all of these, grids too small for them go to the k-split kernel.
+//
+// bf16: the k-split kernel's tile is the one with the least work per CU, rounds
+// of 256 workgroups times operand rows per tile (the rows are what a CU loads).
+// It is taken up to 240 such rows, when 128 x 144 tiles would not fill a round:
+// measured against those tiles (us, K = 1152 / 4608) 4.8 against 16.3 / 10.6
+// against 45.8 at 80 rows (M = 256, N = 1152), 9.7 against 16.6 / 23.2 against
+// 48.0 at 144 (M = 1020, N = 1152); at 288 rows it is 22 against 17 / 54 against
+// 51 (M = 2048).
+// fp32: always (the MFMA is a sixteenth as fast, so the loads hardly matter):
+// 16 x 16 tiles where they make at most four rounds (M = N = 128, K = 512: 3.2 us
+// against 6.3 with 32 x 48 tiles and 53 with the register-staged 128 x 128
+// tile), else 32 x 48 (M = 2048, N = 1500, K = 6144: 275 us, 138 TFLOP/s, against
+// 626 and 464).
+template <typename T, int EPI>
+static bool run_ksplit(const GemmArgs& g, hipStream_t s) {
+    constexpr int BK = 128 / (int)sizeof(T);
+    // Offsets within a tile are 32-bit.
+    if (g.K % BK || (g.lda > g.ldw ? g.lda : g.ldw) > (1 << 20)) return false;
+    auto tiles = [&](int bm, int bn) { return (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
+    const bool vec = vec4_ok(g, EPI);
+    if constexpr (sizeof(T) == 4) {
+        if (tiles(32, 48) > 0x7fffffff) return false;
+        if (tiles(16, 16) <= 4 * 256) launch_ksplit<T, EPI, 1, 1, 8, 1>(g, vec, s);
+        else launch_ksplit<T, EPI, 2, 3, 8, 1>(g, vec, s);
+        return true;
+    } else {
+        auto rows = [&](int bm, int bn) { return (tiles(bm, bn) + 255) / 256 * (bm + bn); };
+        const int64_t r[4] = {rows(32, 48), rows(64, 48), rows(64, 64), rows(64, 80)};
+        int best = 0;
+        for (int i = 1; i < 4; ++i)
+            if (r[i] < r[best]) best = i;
+        if (r[best] > 240 || tiles(128, 144) > 256) return false;
+        switch (best) {
+            case 0: launch_ksplit<T, EPI, 2, 3, 8, 1>(g, vec, s); break;
+            case 1: launch_ksplit<T, EPI, 4, 3, 8, 1>(g, vec, s); break;
+            case 2: launch_ksplit<T, EPI, 4, 4, 8, 1>(g, vec, s); break;
+            default: launch_ksplit<T, EPI, 4, 5, 8, 1>(g, vec, s); break;
+        }
+        return true;
+    }
+}
+
 template <typename T, int EPI>
 static int run_gemm(const GemmArgs& g, hipStream_t s) {
     const int64_t tiles128 = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
     if (tiles128 > 0x7fffffff) return fail(BC_ERR_UNSUPPORTED, "GEMM grid too large");
+    if (run_ksplit<T, EPI>(g, s)) return check_launch("gemm");
     if constexpr (sizeof(T) == 2) {
         const int64_t tiles288 = (int64_t)((g.M + 255) / 256) * ((g.N + 287) / 288);
         const int64_t tiles144 = (int64_t)((g.M + 127) / 128) * ((g.N + 143) / 144);

@@ -147,3 +147,44 @@ def test_attention_rejects_unsupported_head_dim(bclib):
     with pytest.raises(bclib.BCError) as e:
         bclib.attention(z, z, z, torch.empty_like(z))
     assert e.value.code == bclib.ERR_UNSUPPORTED
+
+
+# The k-split linear of small grids, against 64 bits: every tile shape it takes
+# (bf16: 32 x 48, 64 x 48, 64 x 64, 64 x 80; fp32: 16 x 16, 32 x 48), fewer
+# k-steps than waves (64 bf16 / 32 fp32 values a step) and numbers of them that
+# leave the waves unequal shares, ragged rows and columns, columns that are not
+# a multiple of 4 and an output that is not 16-byte aligned (element-wise
+# epilogue), a gate that changes within a tile.
+@pytest.mark.parametrize("epi", ["bias", "gelu", "gate"])
+@pytest.mark.parametrize("dt,M,N,K,off", [
+    ("bf16", 1, 8, 64, 0), ("bf16", 250, 1152, 4608, 0), ("bf16", 256, 3072, 576, 0), ("bf16", 250, 3456, 640, 0),
+    ("bf16", 1020, 1152, 1088, 0), ("bf16", 250, 1151, 576, 0), ("bf16", 70, 300, 192, 2),
+    ("f32", 1, 8, 32, 0), ("f32", 130, 200, 288, 0), ("f32", 600, 900, 160, 0), ("f32", 70, 301, 96, 0),
+    ("f32", 70, 300, 96, 2)])
+def test_linear_small_grids(bclib, dt, M, N, K, off, epi):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M * 7 + N)
+
+    def rnd(*s, scale=1.0):
+        return torch.empty(s, device=DEV).normal_(0.0, scale, generator=g)
+
+    A, W, b = rnd(M, K).to(TDT[dt]), rnd(N, K, scale=0.05).to(TDT[dt]), rnd(N, scale=0.1).to(TDT[dt])
+    y = A.double() @ W.double().T.contiguous() + b.double()
+    odt = torch.float32 if epi == "gate" else TDT[dt]
+    buf = torch.full((M * N + off + 8,), 7.0, dtype=odt, device=DEV)
+    out = buf[off:off + M * N].view(M, N)
+    if epi == "gate":
+        rpg = max(1, M // 3)
+        G, R = rnd((M + rpg - 1) // rpg, N, scale=0.5), rnd(M, N)
+        y = R.double() + G.double().repeat_interleave(rpg, 0)[:M] * y
+        bclib.linear(A, W, b, out, bclib.EPI_GATE_RES, res=R, gate=G, rows_per_gate=rpg)
+    elif epi == "gelu":
+        y = torch.nn.functional.gelu(y, approximate="tanh")
+        bclib.linear(A, W, b, out, bclib.EPI_BIAS_GELU)
+    else:
+        bclib.linear(A, W, b, out)
+    torch.cuda.synchronize()
+    err = float((out.double() - y).norm() / y.norm())
+    # bf16 outputs are rounded once (2^-9 relative at most, 1.7e-3 in the mean); else fp32 sums of K terms
+    assert err <= (2.5e-3 if odt == torch.bfloat16 else 2e-6), err
+    assert bool((buf[:off] == 7.0).all()) and bool((buf[off + M * N:] == 7.0).all())    # nothing written outside
