@@ -120,6 +120,14 @@ static int qproj(int dt, const void* A, int64_t lda, const void* W, const void* 
     return launch_gemm(dt, BC_EPI_BIAS, g, s);
 }
 
+// Rows up to which the QKV projection and the attention of short sequences run
+// as two kernels.  The fused kernel has one workgroup per (sample, head), each
+// with all of the projection's k-steps, so its time does not fall below that of
+// one round: 34 us for one DiT-XL/2 sample (16 workgroups), where the k-split
+// projection and the attention take 9 + 7 us; with four samples (1024 rows) 19 +
+// 7 against 34, with eight about 30 + 9 against 35.
+constexpr int kFusedQkvRows = 1024;
+
 // One DiT or PixArt block on x [B*T, D] (fp32).  mod: [B, >= 6D] fp32 rows
 // ld_mod apart, ordered (shift1, scale1, gate1, shift2, scale2, gate2).
 // sites (blockwise mode): the block's module outputs before their gates
@@ -138,8 +146,8 @@ static int dit_block(const bc_block_desc& d, const bc_block_weights& w, float* x
     a.o0 = a.o1 = bb.attn; a.ldo = D;
     a.B = d.B; a.H = d.heads; a.d = d.head_dim;
     auto al = [](const void* p, int n) { return reinterpret_cast<uintptr_t>(p) % n == 0; };
-    if (qkv_attention_supported(dt, T, d.head_dim, D) && d.heads * d.head_dim == D && al(sw.w_qkv, 16) &&
-        al(sw.b_qkv, 8)) {
+    if (M > kFusedQkvRows && qkv_attention_supported(dt, T, d.head_dim, D) && d.heads * d.head_dim == D &&
+        al(sw.w_qkv, 16) && al(sw.b_qkv, 8)) {
         // Short sequences (DiT-XL/2's 256 tokens): the QKV projection and the
         // self-attention of a (sample, head) in one workgroup, Q, K and V in LDS.
         a.Tq0 = a.Tk0 = T;

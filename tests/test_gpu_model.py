@@ -537,3 +537,12 @@ def test_modulation_linear(bclib, dt, B, heads, hd, off):
     err = float((x.double() - want).norm() / want.norm())
     # bf16: the activation is rounded once (2^-9 relative each, averaged over D terms); fp32: sums of D terms
     assert err <= (3e-3 if dt == "bf16" else 2e-6), err
+
+
+# The fused QKV projection + attention at more than 1024 rows (fewer take the
+# projection and the attention as two kernels): a ragged last key tile and a
+# full one, head dims 64 and 32.
+@pytest.mark.parametrize("hidden,heads,hd,latent,B", [(512, 8, 64, (4, 20, 22), 10), (256, 8, 32, (4, 32, 32), 5)],
+                         ids=["d64_T110_B10", "d32_T256_B5"])
+def test_dit_block_fused_qkv_attention_rows(bclib, hidden, heads, hd, latent, B):
+    test_dit_block_fused_qkv_attention(bclib, hidden, heads, hd, latent, B)
