@@ -12,6 +12,8 @@
 // and accumulates in fp32; lane l ends with rows 4(l/16)..+4 of column l%16.
 // The epilogue applies the bias and then one of: nothing, GELU (tanh form),
 // or the gated residual x + g * y of the adaLN blocks.
+#include <type_traits>
+
 #include "gemm.h"
 
 namespace bc {
@@ -232,6 +234,12 @@ __device__ __forceinline__ int swz(int row) { return swz_of<0>(row); }
 __device__ __forceinline__ void dma16(const void* src, const void* lds_base) {
     const unsigned m0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lds_base);   // wave-uniform
     asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(m0) : "memory", "m0");
+}
+
+// One wave-wide direct-to-LDS load from a wave-uniform base plus a 32-bit byte
+// offset per lane.
+__device__ __forceinline__ void dma16s(const void* base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds) : "memory", "m0");
 }
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
@@ -825,22 +833,426 @@ __device__ __forceinline__ void gemm_wide_body(GemmArgs g, int tile) {
     epilogue_t<EPI, TM, TN>(g, acc, bm + wm * WM, bn + j0 * 16, lane, jn, pf);
 }
 
-template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int BK, int KG, int PIPE = 0>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void gemm_wide_kernel(GemmArgs g) {
-    gemm_wide_body<EPI, BM, BN, WAVES_M, WAVES_N, STAGES, BK, KG, PIPE>(g, xcd_contiguous(blockIdx.x, gridDim.x));
+// ---------------------------------------------------------------------------
+// Phased bf16 kernel: the large tiles, whose loads are spread over the whole
+// k-step.
+//
+// With two whole stages and one barrier per k-step (the wide kernel above) all
+// loads of a stage go out at once and must all be back one step later, and the
+// fragment reads of a step cannot start before its barrier: on 14 566 x 3072 x
+// 15 360 the loads alone took 1058 us of the kernel's 1187.  Here a stage is
+// cut into A halves of 128 rows and W parts of 128 or 96 rows, a wave's output
+// is its share of every (half, part), and a step runs through these pairs in
+// an order in which each keeps one of the last pair's operands in registers.
+// The fragments of the next pair are read under the MFMAs of the present one,
+// and a half or part is loaded again, for the step after the next, as soon as
+// every wave has read it: 1.5 to 1.75 steps of loads are always on their way,
+// and no wait drains them.  Eight waves (two per SIMD) of 128 x 64 (256 x 256
+// tiles: A0 W0, A0 W1, A1 W1, A1 W0) or 64 x 144 (256 x 288: A0 W0, A1 W0,
+// A1 W1, A0 W1, A0 W2, A1 W2), 24 or 26 fragment reads per 64 or 72 MFMAs.
+// Same k order per output as the wide kernel, so the same bits.
+// Measured against it (us): 14 566 x 21 504 x 3072 GELU 1800 -> 1495, 14 310 x
+// 12 288 x 3072 GELU 921 -> 825, 14 566 x 3072 x 15 360 gated 1266 -> 1070,
+// 14 310 x 3072 x 3072 gated 307 -> 276; with 256 x 288 tiles 16 384 x 1152 x
+// 4608 gated 172 -> 155, 16 384 x 4608 x 1152 GELU 172 -> 169.  What bounds it
+// now: the MFMAs are busy 0.67 to 0.78 of the cycles, at the 1.8 to 1.9 GHz that
+// the card's power leaves them.
+// (32 x 32 x 16 MFMAs in the same phases: 10 % slower, two accumulators per
+// phase being too short a chain; s_setprio around the MFMAs, or the reads all
+// ahead of them: 3 to 8 % slower.)
+// Needs at least two k-steps, and offsets within a tile below 4 GB.
+// ---------------------------------------------------------------------------
+enum PhaseStep { PH_MAIN = 0, PH_LAST2 = 1, PH_LAST = 2 };
+
+// NP column parts per tile: 2 for 256 x 256, 3 for 256 x 288.
+template <int NP> struct PhaseTile;
+template <> struct PhaseTile<2> { static constexpr int BN = 256, WAVES_M = 2, WAVES_N = 4; };
+template <> struct PhaseTile<3> { static constexpr int BN = 288, WAVES_M = 4, WAVES_N = 2; };
+
+template <int EPI, int NP>
+__device__ __forceinline__ void gemm_phase_body(const GemmArgs& g, int tile) {
+    typedef PhaseTile<NP> PT;
+    typedef Mma<bf16> MM;
+    constexpr int BM = 256, BN = PT::BN, BK = 64;
+    constexpr int WAVES_M = PT::WAVES_M, WAVES_N = PT::WAVES_N;
+    constexpr int AH = 128, BP = BN / NP;                      // rows of an A half, of a W part
+    constexpr int TM = AH / WAVES_M / 16, TN = BP / WAVES_N / 16;   // a wave's 16 x 16 blocks in one (half, part)
+    static_assert(TM * WAVES_M * 16 == AH && TN * WAVES_N * 16 == BP, "tile split");
+    constexpr int ABYTES = AH * 128, BBYTES = BP * 128;
+    constexpr int OPITCH = BN + 8, STAGES = 2 * (2 * ABYTES + NP * BBYTES);
+    constexpr int SMEM = BM * OPITCH * 2 > STAGES ? BM * OPITCH * 2 : STAGES;
+    __shared__ __attribute__((aligned(1024))) char sm[SMEM];
+    typedef __attribute__((address_space(3))) const char lds_char;
+    typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    const int frow = lane % 16, grp = lane / 16;
+
+    const int tiles_m = (g.M + BM - 1) / BM;
+    const int tiles_n = (g.N + BN - 1) / BN;
+    constexpr int GROUP_M = 8;
+    const int group = GROUP_M * tiles_n;
+    const int first_m = (tile / group) * GROUP_M;
+    const int gm = min(tiles_m - first_m, GROUP_M);
+    const int tm = first_m + (tile % group) % gm;
+    const int tn = (tile % group) / gm;
+    const int bm = tm * BM, bn = tn * BN;
+
+    // LDS: the A halves, then the W parts, each for even and odd k-steps side
+    // by side; rows of 128 bytes, 16-byte chunk c of row r in slot
+    // c ^ ((r >> 1) & 7).  A wave-wide load fills 8 rows: wave w takes loads w
+    // and w + 8 of every half and part (the last four of a 288-column tile's
+    // twelve go to waves 0-3).
+    constexpr int AL = AH / 64, BL = (BP / 8 + 7) / 8;          // loads per wave: of a half, of a part (at most)
+    constexpr bool EVEN = BP / 8 % 8 == 0;
+    const bool more = EVEN || wave < BP / 8 % 8;                // this wave makes BL loads of a part, not BL - 1
+    const uint32_t ldsw = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_char*)sm + wave * 1024);
+    const char* baseA = reinterpret_cast<const char*>(static_cast<const bf16*>(g.A) + (int64_t)bm * g.lda);
+    const char* baseW = reinterpret_cast<const char*>(static_cast<const bf16*>(g.W) + (int64_t)bn * g.ldw);
+    uint32_t offA[2][AL], offW[NP][BL];
+#pragma unroll
+    for (int q = 0; q < (AL > BL ? AL : BL); ++q) {
+        const int r = 64 * q + 8 * wave + (lane >> 3);
+        const uint32_t ch = ((lane & 7) ^ ((r >> 1) & 7)) * 16;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (q < AL) offA[h][q] = (uint32_t)(min(bm + AH * h + r, g.M - 1) - bm) * (uint32_t)(g.lda * 2) + ch;
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            if (q < BL) offW[p][q] = (uint32_t)(min(bn + BP * p + r, g.N - 1) - bn) * (uint32_t)(g.ldw * 2) + ch;
+    }
+    auto loadA = [&](int h, int par, int k) __attribute__((always_inline)) {
+        const char* b = baseA + (int64_t)k * 128;
+#pragma unroll
+        for (int q = 0; q < AL; ++q) dma16s(b, offA[h][q], ldsw + (2 * h + par) * ABYTES + q * 8192);
+    };
+    auto loadW = [&](int p, int par, int k) __attribute__((always_inline)) {
+        const char* b = baseW + (int64_t)k * 128;
+#pragma unroll
+        for (int q = 0; q < BL; ++q)
+            if (EVEN || q + 1 < BL || more) dma16s(b, offW[p][q], ldsw + 4 * ABYTES + (2 * p + par) * BBYTES + q * 8192);
+    };
+    // Waits until at most A loads of A halves and B W parts (counted in loads
+    // of parts) issued after the ones needed are outstanding.
+    auto wait = [&](auto ac, auto bc) __attribute__((always_inline)) {
+        constexpr int A = decltype(ac)::value * AL, B = decltype(bc)::value;
+        if (more) wait_vmcnt<A + B * BL>();
+        else wait_vmcnt<A + B * (EVEN ? BL : BL - 1)>();
+    };
+#define PH_WAIT(A, B) wait(std::integral_constant<int, A>{}, std::integral_constant<int, B>{})
+    // Fragment addresses: a row's swizzle depends only on the row mod 16.
+    lds_char *pA[2], *pW[2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+        const uint32_t c = (uint32_t)((kk * 4 + grp) ^ ((frow >> 1) & 7)) * 16;
+        pA[kk] = (lds_char*)sm + (wm * TM * 16 + frow) * 128 + c;
+        pW[kk] = (lds_char*)sm + 4 * ABYTES + (wn * TN * 16 + frow) * 128 + c;
+    }
+    u32x4 fa[2][TM][2], fw[2][TN][2];     // [half][block][kk]; [register set][block][kk]
+    auto readA = [&](int h, int par) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int i = 0; i < TM; ++i) fa[h][i][kk] = *(lds_u32x4*)(pA[kk] + (2 * h + par) * ABYTES + i * 16 * 128);
+    };
+    auto readW = [&](int p, int par, int set) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fw[set][j][kk] = *(lds_u32x4*)(pW[kk] + (2 * p + par) * BBYTES + j * 16 * 128);
+    };
+    f32x4 acc[2][NP][TM][TN];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[h][p][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto mma = [&](int h, int p, int set) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[h][p][i][j] = MM::mma(__builtin_bit_cast(MM::frag, fw[set][j][kk]),
+                                              __builtin_bit_cast(MM::frag, fa[h][i][kk]), acc[h][p][i][j]);
+    };
+    auto barrier = [&]() __attribute__((always_inline)) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto reads_done = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
+    // A phase's order: its NR fragment reads, each ahead of one MFMA, then the other MFMAs.
+    constexpr int NM = 2 * TM * TN;
+#define PH_ORDER(NR) do { \
+        _Pragma("unroll") for (int z = 0; z < NR; ++z) { __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); } \
+        __builtin_amdgcn_sched_group_barrier(0x008, NM - NR, 0); __builtin_amdgcn_sched_barrier(0); } while (0)
+
+    const int nk = g.K / BK;
+    // One k-step on the buffers of parity PAR, which is also the register set
+    // that holds the step's first W part.
+    auto step = [&](int k, auto parc, auto modec) __attribute__((always_inline)) {
+        constexpr int PAR = decltype(parc)::value, MODE = decltype(modec)::value;
+        constexpr bool MAIN = MODE == PH_MAIN;
+        if constexpr (NP == 2) {
+            if (MAIN) loadA(0, PAR, k + 2);
+            readW(1, PAR, PAR ^ 1);
+            mma(0, 0, PAR);
+            PH_ORDER(2 * TN);
+            if (MAIN) PH_WAIT(3, 2); else if (MODE == PH_LAST2) PH_WAIT(2, 2); else PH_WAIT(0, 0);
+            barrier();
+            if (MAIN) loadW(0, PAR, k + 2);
+            readA(1, PAR);
+            mma(0, 1, PAR ^ 1);
+            PH_ORDER(2 * TM);
+            barrier();
+            if (MAIN) loadW(1, PAR, k + 2);
+            mma(1, 1, PAR ^ 1);
+            if (MODE == PH_LAST) {
+                mma(1, 0, PAR);
+                return;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (MAIN) PH_WAIT(2, 3); else PH_WAIT(1, 1);
+            barrier();
+            if (MAIN) loadA(1, PAR, k + 2);
+            readW(0, PAR ^ 1, PAR ^ 1);
+            readA(0, PAR ^ 1);
+            mma(1, 0, PAR);
+            PH_ORDER(2 * (TM + TN));
+            if (MAIN) PH_WAIT(3, 2); else PH_WAIT(1, 0);
+            reads_done();
+            barrier();
+        } else {
+            if (MAIN) loadA(0, PAR, k + 2);
+            readA(1, PAR);
+            mma(0, 0, PAR);
+            PH_ORDER(2 * TM);
+            if (MAIN) PH_WAIT(3, 4); else if (MODE == PH_LAST2) PH_WAIT(2, 4); else PH_WAIT(0, 1);
+            reads_done();
+            barrier();
+            if (MAIN) loadW(0, PAR, k + 2);
+            readW(1, PAR, PAR ^ 1);
+            mma(1, 0, PAR);
+            PH_ORDER(2 * TN);
+            if (MAIN) loadA(1, PAR, k + 2);
+            mma(1, 1, PAR ^ 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (MAIN) PH_WAIT(4, 4); else if (MODE == PH_LAST2) PH_WAIT(2, 3); else PH_WAIT(0, 0);
+            barrier();
+            if (MAIN) loadW(1, PAR, k + 2);
+            readW(2, PAR, PAR);
+            mma(0, 1, PAR ^ 1);
+            PH_ORDER(2 * TN);
+            mma(0, 2, PAR);
+            if (MODE == PH_LAST) {
+                mma(1, 2, PAR);
+                return;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (MAIN) PH_WAIT(3, 4); else PH_WAIT(1, 2);
+            barrier();
+            if (MAIN) loadW(2, PAR, k + 2);
+            readW(0, PAR ^ 1, PAR ^ 1);
+            readA(0, PAR ^ 1);
+            mma(1, 2, PAR);
+            PH_ORDER(2 * (TM + TN));
+            if (MAIN) PH_WAIT(2, 5); else PH_WAIT(0, 2);
+            reads_done();
+            barrier();
+        }
+    };
+    typedef std::integral_constant<int, 0> C0;
+    typedef std::integral_constant<int, 1> C1;
+    typedef std::integral_constant<int, 2> C2;
+    auto load_step = [&](auto parc, int k) __attribute__((always_inline)) {
+        constexpr int PAR = decltype(parc)::value;
+        loadA(0, PAR, k);
+        loadW(0, PAR, k);
+        if constexpr (NP == 2) {
+            loadW(1, PAR, k);
+            loadA(1, PAR, k);
+        } else {
+            loadA(1, PAR, k);
+            loadW(1, PAR, k);
+            loadW(2, PAR, k);
+        }
+    };
+    auto first = [&](auto parc) __attribute__((always_inline)) {
+        constexpr int PAR = decltype(parc)::value;
+        load_step(parc, 0);
+        load_step(std::integral_constant<int, PAR ^ 1>{}, 1);
+        if constexpr (NP == 2) PH_WAIT(3, 2); else PH_WAIT(2, 5);
+        barrier();
+        readA(0, PAR);
+        readW(0, PAR, PAR);
+        reads_done();
+        barrier();
+    };
+    // An odd number of steps starts on the odd buffers, so that the last two
+    // steps always run on the even, then the odd ones.
+    const int odd = nk & 1;
+    if (odd) {
+        first(C1{});
+        step(0, C1{}, C0{});
+    } else {
+        first(C0{});
+    }
+    int k = odd;
+    for (; k + 2 < nk; k += 2) {
+        step(k, C0{}, C0{});
+        step(k + 1, C1{}, C0{});
+    }
+    step(k, C0{}, C1{});
+    step(k + 1, C1{}, C2{});
+#undef PH_ORDER
+#undef PH_WAIT
+
+    // A lane holds, of each block, four consecutive columns of one row.
+    const GemmEpi& e = g.e;
+    const bf16* __restrict__ bias = static_cast<const bf16*>(e.bias);
+    auto lrow_of = [&](int h, int i) __attribute__((always_inline)) { return AH * h + (wm * TM + i) * 16 + frow; };
+    auto lcol_of = [&](int p, int j) __attribute__((always_inline)) { return BP * p + (wn * TN + j) * 16 + 4 * grp; };
+    auto bias4 = [&](int col, float (&bv)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bv[r] = 0.f;
+        if (bias && col < g.N) {
+            const bf16x4 b4 = *reinterpret_cast<const bf16x4*>(bias + col);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) bv[r] = (float)b4[r];
+        }
+    };
+    if constexpr (EPI == BC_EPI_GATE_RES) {
+        // Straight from the accumulators, one (half, part) after the other,
+        // the residual of the next one requested before the present one is
+        // stored: the stream is updated in place, so no load is moved
+        // over a store by itself.
+        f32x4 rv[2][TM][TN], gv[TN];
+        // One sample's gate for the whole tile (else read row by row).
+        const bool one_gate = e.gate && bm / e.rows_per_gate == min(bm + BM - 1, g.M - 1) / e.rows_per_gate;
+        auto fetch = [&](int u) __attribute__((always_inline)) {
+            const int h = u / NP, p = u % NP;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int col = min(bn + lcol_of(p, j), g.N - 4);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    rv[u & 1][i][j] = *reinterpret_cast<const f32x4*>(e.res + (int64_t)min(bm + lrow_of(h, i), g.M - 1) * e.ldr + col);
+            }
+        };
+        fetch(0);
+#pragma unroll
+        for (int u = 0; u < 2 * NP; ++u) {
+            const int h = u / NP, p = u % NP;
+            if (u + 1 < 2 * NP) fetch(u + 1);
+            if (one_gate) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    gv[j] = *reinterpret_cast<const f32x4*>(e.gate + (int64_t)(bm / e.rows_per_gate) * e.ldg + min(bn + lcol_of(p, j), g.N - 4));
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const int row = bm + lrow_of(h, i);
+                const int b = row / e.seg, sidx = row - b * e.seg;
+                const bool row_ok = row < g.M && sidx < e.keep;
+                const int64_t orow = (int64_t)(b * e.keep + sidx) * e.ldo;
+                const float* grow = e.gate && !one_gate && row_ok ? e.gate + (int64_t)(row / e.rows_per_gate) * e.ldg : nullptr;
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const int col = bn + lcol_of(p, j);
+                    if (!row_ok || col >= g.N) continue;
+                    float bv[4], v[4];
+                    bias4(col, bv);
+                    const f32x4 gt = one_gate ? gv[j] : grow ? *reinterpret_cast<const f32x4*>(grow + col)
+                                                                    : f32x4{1.f, 1.f, 1.f, 1.f};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] = rv[u & 1][i][j][r] + gt[r] * (acc[h][p][i][j][r] + bv[r]);
+                    if (e.out_f32) st4(static_cast<float*>(e.out) + orow + col, v);
+                    else st4(static_cast<bf16*>(e.out) + orow + col, v);
+                }
+            }
+        }
+    } else {
+        // The bias kind.  bf16: as in gemm_wide_body the finished tile goes
+        // through LDS, row-major, and leaves as consecutive 16-byte chunks of
+        // its rows.  fp32: straight from the accumulators.
+        bf16* so = reinterpret_cast<bf16*>(sm);
+        __syncthreads();   // every wave is done with the stage buffers
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int lc = lcol_of(p, j), col = bn + lc;
+                float bv[4];
+                bias4(col, bv);
+                const bool act = col >= e.gelu_from;
+                const float qs = col < e.q_scale_to ? e.q_scale : 1.f;
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        float v[4];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            v[r] = (acc[h][p][i][j][r] + bv[r]) * qs;
+                            if (act) v[r] = gelu_tanh(v[r]);
+                        }
+                        const int lr = lrow_of(h, i);
+                        if (!e.out_f32) st4(so + lr * OPITCH + lc, v);
+                        else if (bm + lr < g.M && col < g.N) {     // (the split part is in the operand dtype)
+                            if (col >= e.split) st4(static_cast<bf16*>(e.out2) + (int64_t)(bm + lr) * e.ldo2 + (col - e.split + e.off2), v);
+                            else st4(static_cast<float*>(e.out) + (int64_t)(bm + lr) * e.ldo + col, v);
+                        }
+                    }
+            }
+        if (e.out_f32) return;
+        __syncthreads();
+        constexpr int CPRO = BN / 8;
+#pragma unroll 4
+        for (int q = tid; q < BM * CPRO; q += 512) {
+            const int lr = q / CPRO, c8 = q - lr * CPRO;
+            const int row = bm + lr, col = bn + c8 * 8;
+            if (row >= g.M || col >= g.N) continue;
+            const u32x4 val = *reinterpret_cast<const u32x4*>(so + lr * OPITCH + c8 * 8);
+            bf16* dst = col >= e.split ? static_cast<bf16*>(e.out2) + (int64_t)row * e.ldo2 + (col - e.split + e.off2)
+                                       : static_cast<bf16*>(e.out) + (int64_t)row * e.ldo + col;
+            *reinterpret_cast<u32x4*>(dst) = val;
+        }
+    }
+}
+
+template <int EPI, int NP>
+__global__ __launch_bounds__(512) void gemm_phase_kernel(GemmArgs g) {
+    gemm_phase_body<EPI, NP>(g, xcd_contiguous(blockIdx.x, gridDim.x));
 }
 
 // Two GEMMs in one grid: workgroups [0, tiles0) take the first (in the
 // XCD-contiguous order over its own tiles), the rest the second, whose
 // workgroups come last and are dealt round-robin to the XCDs, so its tiles
 // fill the first one's last round.
-template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int BK, int KG, int PIPE = 0>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void gemm_wide_pair_kernel(GemmArgs g0, GemmArgs g1,
-                                                                                     int tiles0) {
+template <int EPI>
+__global__ __launch_bounds__(512) void gemm_phase_pair_kernel(GemmArgs g0, GemmArgs g1, int tiles0) {
     const int b = blockIdx.x;
     const bool second = b >= tiles0;
-    gemm_wide_body<EPI, BM, BN, WAVES_M, WAVES_N, STAGES, BK, KG, PIPE>(second ? g1 : g0,
-                                                                        second ? b - tiles0 : xcd_contiguous(b, tiles0));
+    gemm_phase_body<EPI, 2>(second ? g1 : g0, second ? b - tiles0 : xcd_contiguous(b, tiles0));
+}
+
+template <int EPI, int NP>
+static void launch_phase(const GemmArgs& g, hipStream_t s) {
+    constexpr int BN = PhaseTile<NP>::BN;
+    launch_k(gemm_phase_kernel<EPI, NP>, dim3((unsigned)(((g.M + 255) / 256) * ((g.N + BN - 1) / BN))), dim3(512), s, g);
+}
+
+template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int BK, int KG, int PIPE = 0>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void gemm_wide_kernel(GemmArgs g) {
+    gemm_wide_body<EPI, BM, BN, WAVES_M, WAVES_N, STAGES, BK, KG, PIPE>(g, xcd_contiguous(blockIdx.x, gridDim.x));
 }
 
 template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES = 2, int BK = 64, int KG = 1, int PIPE = 0>
@@ -883,12 +1295,6 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
 // of that: the 16 lanes of a fragment row fetch from 16 rows, 16 bytes each.)
 // Any N and alignment of the outputs (vec: 4-column accesses are possible).
 // ---------------------------------------------------------------------------
-// One wave-wide direct-to-LDS load from a wave-uniform base plus a 32-bit byte
-// offset per lane.
-__device__ __forceinline__ void dma16s(const void* base, uint32_t off, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds) : "memory", "m0");
-}
-
 template <typename T> struct KsMma;
 template <> struct KsMma<bf16> {
     __device__ static __forceinline__ f32x4 mma(const u32x4& w, const u32x4& a, const f32x4& c) {
@@ -1102,12 +1508,26 @@ static bool wide_ok(const GemmArgs& g, int epi) {
     return true;
 }
 
+// Column parts of the phased kernel's tile (2: 256 x 256, 3: 256 x 288), or 0
+// where its tiles do not make a round over the 256 CUs (see the choice below).
+// A round of 256 x 256 tiles takes about 1.34 us per k-step and 11 us for the
+// prologue and epilogue, one of 256 x 288 tiles 1.58 and 14 (from K = 1152 and
+// 3072 at 14 310 and 16 384 rows); the tile with the least rounds times that:
+// 16 384 x 4608 x 1152 177 against 169 us (5 against 4 rounds), 5000 x 4608 x
+// 1152 66 against 77 (2 rounds each).
+static int phase_parts(const GemmArgs& g) {
+    const int64_t tm = (g.M + 255) / 256, t256 = tm * ((g.N + 255) / 256), t288 = tm * ((g.N + 287) / 288);
+    const int nk = g.K / 64;
+    if (t288 < 256 || nk < 2 || (g.lda > g.ldw ? g.lda : g.ldw) > (1 << 22)) return 0;
+    const double c2 = (double)((t256 + 255) / 256) * (1.34 * nk + 11), c3 = (double)((t288 + 255) / 256) * (1.58 * nk + 14);
+    return c2 <= c3 ? 2 : 3;
+}
+
 // Tile choice (measured on MI355X over the DiT-XL/2, PixArt and HunyuanVideo
 // block shapes, see the design notes), for bf16 operands with whole 64-wide
 // k-steps and an epilogue the wide kernel can vectorise:
-//   * at least one full round of 256 x 288 tiles over the 256 CUs: 256 x 288
-//     (8 waves of 64 x 144), or 256 x 256 when N is a multiple of 256 but not
-//     of 288 (no ragged column tile);
+//   * at least one full round of 256 x 288 tiles over the 256 CUs: the phased
+//     kernel;
 //   * N a multiple of 432 with at least one round of 128 x 432 tiles (the
 //     DiT-XL/2 QKV projection: exactly 256): 2 x 4 waves of 64 x 112 / 64 x 96;
 //   * at most 256 tiles of 128 x 144 (the N = 1152 projections at M = 4096):
@@ -1168,13 +1588,14 @@ static int run_gemm(const GemmArgs& g, hipStream_t s) {
     if (tiles128 > 0x7fffffff) return fail(BC_ERR_UNSUPPORTED, "GEMM grid too large");
     if (run_ksplit<T, EPI>(g, s)) return check_launch("gemm");
     if constexpr (sizeof(T) == 2) {
-        const int64_t tiles288 = (int64_t)((g.M + 255) / 256) * ((g.N + 287) / 288);
         const int64_t tiles144 = (int64_t)((g.M + 127) / 128) * ((g.N + 143) / 144);
         const bool dma = g.K % 64 == 0 && g.lda % 8 == 0 && g.ldw % 8 == 0;
         if (dma && wide_ok(g, EPI)) {
-            if (tiles288 >= 256) {
-                if (g.N % 288 != 0 && g.N % 256 == 0) launch_wide<EPI, 256, 256, 4, 4>(g, s);
-                else launch_wide<EPI, 256, 288, 4, 3>(g, s);
+            const int parts = phase_parts(g);
+            if (parts == 2) {
+                launch_phase<EPI, 2>(g, s);
+            } else if (parts == 3) {
+                launch_phase<EPI, 3>(g, s);
             } else if (g.N % 432 == 0 && (int64_t)((g.M + 127) / 128) * (g.N / 432) >= 256) {
                 launch_wide<EPI, 128, 432, 4, 3>(g, s);
             } else if (tiles144 <= 256) {
@@ -1245,8 +1666,8 @@ int launch_gemm(int dtype, int epi, const GemmArgs& g, hipStream_t s) {
     return rc;
 }
 
-// The first GEMM's tile choice must be 256 x 256 (as run_gemm picks it) and
-// the second one's tiles must fit the idle part of the first one's last
+// The first GEMM's tile choice must be the phased kernel's 256 x 256 (as
+// run_gemm picks it), the second one must suit that kernel, and its tiles must fit the idle part of the first one's last
 // round; otherwise two launches.
 int launch_gemm_pair(int dtype, int epi, const GemmArgs& g0, const GemmArgs& g1, hipStream_t s) {
     if (g1.M <= 0 || g1.N <= 0) return launch_gemm(dtype, epi, g0, s);
@@ -1257,21 +1678,20 @@ int launch_gemm_pair(int dtype, int epi, const GemmArgs& g0, const GemmArgs& g1,
     };
     const int64_t t0 = (int64_t)((g0.M + 255) / 256) * ((g0.N + 255) / 256);
     const int64_t t1 = (int64_t)((g1.M + 255) / 256) * ((g1.N + 255) / 256);
-    const int64_t t288 = (int64_t)((g0.M + 255) / 256) * ((g0.N + 287) / 288);
     const int64_t idle = (t0 + 255) / 256 * 256 - t0;
-    const bool big = t288 >= 256 && g0.N % 288 != 0 && g0.N % 256 == 0;
-    if (!(wide(g0) && wide(g1) && big && t1 <= idle && t0 + t1 <= 0x7fffffff)) {
+    const bool fits = g1.K >= 128 && (g1.lda > g1.ldw ? g1.lda : g1.ldw) <= (1 << 22);
+    if (!(wide(g0) && wide(g1) && phase_parts(g0) == 2 && fits && t1 <= idle && t0 + t1 <= 0x7fffffff)) {
         const int rc = launch_gemm(dtype, epi, g0, s);
         return rc != BC_OK ? rc : launch_gemm(dtype, epi, g1, s);
     }
     const int cls = epi == BC_EPI_GATE_RES ? (g0.K > g0.N ? PROF_GEMM_DOWN : PROF_GEMM_GATE)
                     : g0.e.gelu_from < g0.N ? PROF_GEMM_GELU : PROF_GEMM_BIAS;
     prof_begin(cls, s, 2.0 * g0.M * (double)g0.N * g0.K + 2.0 * g1.M * (double)g1.N * g1.K);
-    const dim3 grid((unsigned)(t0 + t1)), block(1024);
+    const dim3 grid((unsigned)(t0 + t1)), block(512);
     if (epi == BC_EPI_GATE_RES)
-        launch_k(gemm_wide_pair_kernel<BC_EPI_GATE_RES, 256, 256, 4, 4, 2, 64, 1, 0>, grid, block, s, g0, g1, (int)t0);
+        launch_k(gemm_phase_pair_kernel<BC_EPI_GATE_RES>, grid, block, s, g0, g1, (int)t0);
     else
-        launch_k(gemm_wide_pair_kernel<BC_EPI_BIAS, 256, 256, 4, 4, 2, 64, 1, 0>, grid, block, s, g0, g1, (int)t0);
+        launch_k(gemm_phase_pair_kernel<BC_EPI_BIAS>, grid, block, s, g0, g1, (int)t0);
     prof_end(cls, s);
     return check_launch("gemm pair");
 }

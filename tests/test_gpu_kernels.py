@@ -188,3 +188,14 @@ def test_linear_small_grids(bclib, dt, M, N, K, off, epi):
     # bf16 outputs are rounded once (2^-9 relative at most, 1.7e-3 in the mean); else fp32 sums of K terms
     assert err <= (2.5e-3 if odt == torch.bfloat16 else 2e-6), err
     assert bool((buf[:off] == 7.0).all()) and bool((buf[off + M * N:] == 7.0).all())    # nothing written outside
+
+
+# The phased kernel of large grids against 64 bits: 256 x 256 tiles (4100 x 4352)
+# and 256 x 288 (4090 x 4600), ragged rows and columns, 2 to 7 k-steps (its
+# prologue, its last two steps, and both parities of the main loop), a gate that
+# changes within a tile.
+@pytest.mark.parametrize("epi", ["bias", "gelu", "gate"])
+@pytest.mark.parametrize("M,N,K", [(4100, 4352, 128), (4100, 4352, 192), (4100, 4352, 256), (4100, 4352, 448),
+                                   (4090, 4600, 128), (4090, 4600, 192), (4090, 4600, 256), (4090, 4600, 448)])
+def test_linear_large_grids(bclib, M, N, K, epi):
+    test_linear_small_grids(bclib, "bf16", M, N, K, 0, epi)
