@@ -15,6 +15,7 @@
 // streams of joint attention): position p of sample b is row b*T0 + p of
 // segment 0 if p < T0, else row b*T1 + (p - T0) of segment 1.  Head h of a row
 // is the d consecutive elements starting at column h*d.
+#include <cmath>
 #include <type_traits>
 #include "attention.h"
 
@@ -314,10 +315,10 @@ template <int HD> struct KvLayout {
     __device__ static int at(int row, int d) { return row * HD + slot(row, d >> 3) * 8 + (d & 7); }
 };
 
-// NWV waves of 16 QG queries each per workgroup; NB K/V tile buffers.  When
-// all key tiles fit in the NB buffers they are loaded once, up front, and the
-// key loop runs without further barriers; otherwise two of the buffers are
-// used as a double buffer.
+// NWV waves of 16 QG queries each per workgroup; NB K/V tile buffers.  STREAM
+// false: all key tiles fit in the NB buffers (the launcher sees to it); they
+// are loaded once, up front, and the key loop runs without further barriers.
+// STREAM: the NB = 2 buffers are a double buffer.
 // Reductions over the four lanes l, l ^ 16, l ^ 32, l ^ 48 that hold one
 // query's scores: with both operands equal, v_permlane16_swap returns the
 // value of lane l in one result and of lane l ^ 16 in the other (likewise
@@ -593,11 +594,10 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
         }
     };
     const int ntiles = (Tk + kKTile - 1) / kKTile;
-    const bool resident = ntiles <= NB;
     // K/V loads go out first so that their latency overlaps the Q loads.
     if constexpr (QKV) {
         // (K and V are in LDS already.)
-    } else if (resident) {
+    } else if (!STREAM) {
         for (int t = 0; t < ntiles; ++t) issue_rows(t * kKTile, t);
     } else {
         issue(0, 0);
@@ -623,7 +623,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
     const bool o8 = (a.ldo & 3) == 0 && ((reinterpret_cast<uintptr_t>(a.o0) | reinterpret_cast<uintptr_t>(a.o1)) & 7) == 0;
 #pragma unroll
     for (int g = 0; g < QG; ++g) {
-        m_run[g] = QS ? 0.f : -INFINITY;     // the pre-scaled streaming tile's reference starts at 0
+        m_run[g] = STREAM ? 0.f : -INFINITY;     // the streaming tile's reference is set by its first tile
         osum[g] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < S::DV / 16; ++i) o[g][i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -676,22 +676,17 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
         }
     };
 
-    // Scores, online softmax and the P V update of one 64-key tile at k0, for
-    // queries not pre-scaled (scores times c in one FMA with the max).
-    // Keys past Tk occur in the last tile only.  Two ways to mask them:
-    //   * branch (the streaming loop of the STREAM instantiations): after the
-    //     MFMAs, their scores are set to -inf under a branch taken once per
-    //     workgroup, so the other tiles spend no instructions on the mask;
-    //   * select (otherwise): their score accumulators start at -inf, one
-    //     select per score slot shared by the query groups, which keeps the
-    //     tile one basic block for the scheduler.
-    auto tile = [&](int k0, const bf16* K, const bf16* V, auto branch_mask) __attribute__((always_inline)) {
-        constexpr bool BRANCH = decltype(branch_mask)::value;
+    // Scores, online softmax and the P V update of one resident 64-key tile at
+    // k0 (scores times c in one FMA with the max; c is 1 for pre-scaled
+    // queries).  Keys past Tk occur in the last tile only; their score
+    // accumulators start at -inf, one select per score slot shared by the query
+    // groups, which keeps the tile one basic block for the scheduler.
+    auto tile = [&](int k0, const bf16* K, const bf16* V) __attribute__((always_inline)) {
         f32x4 init[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) init[j][r] = BRANCH || k0 + 16 * j + 4 * grp + r < Tk ? 0.f : -INFINITY;
+            for (int r = 0; r < 4; ++r) init[j][r] = k0 + 16 * j + 4 * grp + r < Tk ? 0.f : -INFINITY;
 
         f32x4 s[QG][4];
 #pragma unroll
@@ -706,17 +701,6 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
                 for (int g = 0; g < QG; ++g) s[g][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[g][c], s[g][j], 0, 0, 0);
             }
         }
-        if (BRANCH && k0 + kKTile > Tk) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (k0 + 16 * j + 4 * grp + r >= Tk) {
-#pragma unroll
-                        for (int g = 0; g < QG; ++g) s[g][j][r] = -INFINITY;
-                    }
-        }
-
         // Softmax in the log2 domain on raw scores (the scale is positive, so
         // the row max can be taken before scaling and folded into one FMA).
         // The reference max m_run moves only when some lane's row max exceeds
@@ -751,15 +735,17 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
         pv((lds_char*)V, s);
     };
 
-    // Streaming tile for pre-scaled queries (QS: q already carries the factor
-    // c = log2(e) / sqrt(d)), so the MFMA yields scores in log2 units.  Each
-    // group's score accumulators start at -m (m: the group's reference max),
-    // so the MFMA output is already s c - m and p = 2^(output): no per-score
-    // FMA.  The reference moves (by the tile's excess, with O and the row
-    // sums rescaled) on the first tile and whenever some lane's tile max
-    // exceeds it by more than 8, which keeps p < 2^8.  Keys past Tk occur only
-    // in the last tile; their scores are set to -inf under a branch.  The row
-    // max takes 8 three-input maxima for the 16 scores of a lane.
+    // Streaming tile.  The reference max m of a query moves (with O and the row
+    // sums rescaled) on the first tile and whenever one of a lane's scores
+    // exceeds it by more than 8 (log2 units), which keeps p < 2^8.  Keys past
+    // Tk occur only in the last tile; their scores are set to -inf under a
+    // branch.  The row max takes 8 three-input maxima for the 16 scores of a
+    // lane.
+    // Pre-scaled queries (QS: q already carries the factor c = log2(e) /
+    // sqrt(d)): the MFMA yields scores in log2 units, and each group's score
+    // accumulators start at -m, so its output is already s c - m and
+    // p = 2^(output), no per-score FMA.  Otherwise they start at 0 and
+    // p = 2^(s c - m c), one FMA per score.
     f32x4 negm[QG];
 #pragma unroll
     for (int g = 0; g < QG; ++g) negm[g] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -804,40 +790,46 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
         }
         // The test needs no cross-lane max: some lane over the threshold is
         // enough, and only the (rare) rescale reduces over a query's lanes.
-        float lane_top = mloc[0];
+        const float sc = QS ? 1.f : a.scale_log2;
+        float lane_top = QS ? mloc[0] : (mloc[0] - m_run[0]) * sc;      // excess over the reference, log2 units
 #pragma unroll
-        for (int g = 1; g < QG; ++g) lane_top = vmax(lane_top, mloc[g]);
+        for (int g = 1; g < QG; ++g) lane_top = vmax(lane_top, QS ? mloc[g] : (mloc[g] - m_run[g]) * sc);
         if (__any(first || lane_top > 8.0f)) {
 #pragma unroll
             for (int g = 0; g < QG; ++g) {
-                const float qmax = group_max(mloc[g]);
+                const float qmax = QS ? group_max(mloc[g]) : group_max(mloc[g]) - m_run[g];
                 const float shift = first ? qmax : vmax(qmax, 0.f);
                 m_run[g] += shift;
-                negm[g] = f32x4{-m_run[g], -m_run[g], -m_run[g], -m_run[g]};
+                if constexpr (QS) negm[g] = f32x4{-m_run[g], -m_run[g], -m_run[g], -m_run[g]};
                 if (!first) {
-                    const float alpha = __builtin_amdgcn_exp2f(-shift);
+                    const float alpha = __builtin_amdgcn_exp2f(-shift * sc);
                     if constexpr (!PADSUM) osum[g] *= alpha;
 #pragma unroll
                     for (int i = 0; i < S::DV / 16; ++i) o[g][i] *= alpha;
                 }
+                if constexpr (QS) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) s[g][j] -= shift;
+                    for (int j = 0; j < 4; ++j) s[g][j] -= shift;
+                }
             }
         }
 #pragma unroll
-        for (int g = 0; g < QG; ++g)
+        for (int g = 0; g < QG; ++g) {
+            const float mc = m_run[g] * sc;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) s[g][j][r] = __builtin_amdgcn_exp2f(s[g][j][r]);
+                for (int r = 0; r < 4; ++r)
+                    s[g][j][r] = __builtin_amdgcn_exp2f(QS ? s[g][j][r] : __builtin_fmaf(s[g][j][r], sc, -mc));
+        }
         pv(Vb, s);
     };
 
-    if (resident) {
+    if constexpr (!STREAM) {
         __builtin_amdgcn_s_waitcnt((0 & 15) | (7 << 4) | (15 << 8));   // vmcnt(0): this wave's loads
         __syncthreads();
-        for (int t = 0; t < ntiles; ++t) tile(t * kKTile, sK[t], sV[t], std::false_type{});
-    } else if constexpr (STREAM && QS) {
+        for (int t = 0; t < ntiles; ++t) tile(t * kKTile, sK[t], sV[t]);
+    } else {
         // Unrolled by two so that each step's buffer is a compile-time constant.
         auto step = [&](int t, auto bufc) __attribute__((always_inline)) {
             constexpr int BUF = decltype(bufc)::value;
@@ -849,14 +841,6 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
         for (int t = 0; t < ntiles; t += 2) {
             step(t, std::integral_constant<int, 0>{});
             if (t + 1 < ntiles) step(t + 1, std::integral_constant<int, 1>{});
-        }
-    } else {
-        for (int t = 0; t < ntiles; ++t) {
-            const int buf = t & 1;
-            __builtin_amdgcn_s_waitcnt((0 & 15) | (7 << 4) | (15 << 8));   // vmcnt(0): this wave's loads of tile t
-            __syncthreads();
-            if (t + 1 < ntiles) issue((t + 1) * kKTile, buf ^ 1);
-            tile(t * kKTile, sK[buf], sV[buf], std::integral_constant<bool, STREAM>{});
         }
     }
 
@@ -949,35 +933,43 @@ int launch_attention(int dtype, AttnArgs a, hipStream_t s) {
     a.scale_log2 = a.q_scaled ? 1.0f : attn_q_scale(a.d);
     prof_begin(PROF_ATTENTION, s, 4.0 * a.B * a.H * (double)(a.Tq0 + a.Tq1) * (double)(a.Tk0 + a.Tk1) * a.d);
     // The direct-to-LDS kernel needs 16-byte aligned Q/K/V rows (checked above).
-    // Up to 256 keys: 8 waves with every key tile resident in LDS (one load,
-    // no barriers in the key loop), 32 queries each when that still leaves two
-    // rounds of 256-query workgroups (PixArt's cross-attention to 120 keys at
-    // batch 4: 35.1 -> 28.7 us in a probe, 59.6 -> 58.5 ms of attention per
-    // sampling run), else 16 (DiT-XL/2's self-attention, one round of
-    // 256-query workgroups: 15.2 -> 14.0 us in a probe, but not faster in the
-    // sampling loop); longer sequences: waves
-    // over a double buffer, 64 queries each for d <= 72 (every K/V fragment
-    // read from LDS feeds four MFMAs; 8 waves) and 32 for d = 128 (64 would
-    // not fit the registers; pre-scaled queries in 4-wave workgroups, two per
-    // CU, which ran 24 x 14 566 tokens 6 % faster than one 8-wave workgroup),
-    // fewer when that would leave the grid short of workgroups.
+    // Up to 256 keys, every key tile is resident in LDS (one load, no barriers
+    // in the key loop): 8 waves of 32 queries when that still leaves two rounds
+    // of 256-query workgroups (PixArt's cross-attention to 120 keys at batch 4:
+    // 35.1 -> 28.7 us in a probe, 59.6 -> 58.5 ms of attention per sampling
+    // run), 4 waves of 16 when those make at most one round (one DiT-XL/2
+    // sample: 6.5 us against 7.4 with 8 waves), else 8 waves of 16 (DiT-XL/2's
+    // self-attention at batch 16: 13.9 us against 17.6 with 4 waves).
+    // Longer sequences, waves over a double buffer: 8 waves of 64 queries
+    // (d <= 72: every K/V fragment read from LDS feeds four MFMAs; at d = 128
+    // they would spill), 4 waves of 32, or 4 of 16; the one whose fullest CU
+    // (rounds of 256 workgroups times queries each) finishes first at the rate
+    // that it reaches on a full grid (4 x 16 x 4096^2 x 72: 1014, 965 and 733
+    // TFLOP/s; 550 for 4 x 16 at d = 128, where two workgroups fill a CU's LDS: 24
+    // heads of 1846^2 71 us against 56 with 4 x 32).  2 x 16 x 2050^2 x 64, unscaled: 4 x 32 queries in 63 us, 4 x 16
+    // in 65, 8 x 32 in 99; 1 x 16 x 1020^2 x 72: 4 x 16 in 16.4 us, 4 x 32 in
+    // 20.1; at d = 128 two 4-wave workgroups a CU, whose barriers do not line
+    // up, ran 24 x 14 566 tokens 6 % faster than one of 8 waves.
     int rc;
     if (dtype == BC_BF16) {
         const int Tk = a.Tk0 + a.Tk1, Tq = a.Tq0 + a.Tq1;
-        // Workgroups of 128 / 256 / 512 queries; the larger shapes only when
-        // they still give the grid a full round of workgroups.
         const int64_t bh = (int64_t)a.B * a.H;
-        const int64_t n512 = (Tq + 511) / 512 * bh, n256 = (Tq + 255) / 256 * bh;
-        if (Tk <= 4 * kKTile && n256 >= 512) rc = run_attention_dma<2, 8, 4, false>(a, a.d, s);
-        else if (Tk <= 4 * kKTile) rc = run_attention_dma<1, 8, 4, false>(a, a.d, s);
-        else if (a.d <= 72 && n512 >= 256)
-            rc = a.q_scaled ? run_attention_dma<4, 8, 2, true, true>(a, a.d, s) : run_attention_dma<4, 8, 2>(a, a.d, s);
-        else if (n256 >= 128 && a.d == 128 && a.q_scaled)
-            rc = run_attention_dma<2, 4, 2, true, true>(a, a.d, s);
-        else if (n256 >= 128)
-            rc = a.q_scaled ? run_attention_dma<2, 8, 2, true, true>(a, a.d, s) : run_attention_dma<2, 8, 2>(a, a.d, s);
-        else
-            rc = a.q_scaled ? run_attention_dma<1, 8, 2, true, true>(a, a.d, s) : run_attention_dma<1, 8, 2>(a, a.d, s);
+        auto wgs = [&](int queries) { return (Tq + queries - 1) / queries * bh; };
+        if (Tk <= 4 * kKTile) {
+            if (wgs(256) >= 512) rc = run_attention_dma<2, 8, 4, false>(a, a.d, s);
+            else if (wgs(64) <= 256) rc = run_attention_dma<1, 4, 4, false>(a, a.d, s);
+            else rc = run_attention_dma<1, 8, 4, false>(a, a.d, s);
+        } else {
+            auto cost = [&](int queries, double rate) { return (double)((wgs(queries) + 255) / 256 * queries) / rate; };
+            const double c64 = a.d <= 72 ? cost(512, 1014) : INFINITY, c32 = cost(128, 965),
+                         c16 = cost(64, a.d <= 72 ? 733 : 550);
+            if (c64 <= c32 && c64 <= c16)
+                rc = a.q_scaled ? run_attention_dma<4, 8, 2, true, true>(a, a.d, s) : run_attention_dma<4, 8, 2>(a, a.d, s);
+            else if (c32 <= c16)
+                rc = a.q_scaled ? run_attention_dma<2, 4, 2, true, true>(a, a.d, s) : run_attention_dma<2, 4, 2>(a, a.d, s);
+            else
+                rc = a.q_scaled ? run_attention_dma<1, 4, 2, true, true>(a, a.d, s) : run_attention_dma<1, 4, 2>(a, a.d, s);
+        }
     } else {
         rc = run_attention<float, 1>(a, a.d, s);
     }

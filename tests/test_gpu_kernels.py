@@ -199,3 +199,26 @@ def test_linear_small_grids(bclib, dt, M, N, K, off, epi):
                                    (4090, 4600, 128), (4090, 4600, 192), (4090, 4600, 256), (4090, 4600, 448)])
 def test_linear_large_grids(bclib, M, N, K, epi):
     test_linear_small_grids(bclib, "bf16", M, N, K, 0, epi)
+
+
+# The streaming attention's workgroups of 4 waves: 16 and 32 queries per wave by
+# the size of the grid, queries one past a tile, key tiles of one key; and the
+# resident ones of 4 waves (at most 256 workgroups of 64 queries).
+@pytest.mark.parametrize("prescaled", [False, True])
+@pytest.mark.parametrize("B,H,Tq,Tk,d", [
+    (1, 2, 65, 257, 64), (1, 4, 1020, 300, 72), (2, 16, 1025, 321, 64), (1, 24, 1025, 385, 128), (1, 2, 129, 513, 128),
+    (1, 3, 65, 256, 128), (1, 3, 70, 65, 32), (2, 30, 129, 640, 32)])
+def test_attention_four_waves(bclib, prescaled, B, H, Tq, Tk, d):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(Tq + d)
+    q, k, v = (torch.empty((B, T, H, d), device=DEV).normal_(0.0, 2.0, generator=g).bfloat16() for T in (Tq, Tk, Tk))
+    scale = np.log(2.0) if prescaled else d ** -0.5
+    if prescaled:
+        q = (q.float() * (1.4426950408889634 / d ** 0.5)).bfloat16()
+    t = [a.double().permute(0, 2, 1, 3).contiguous() for a in (q, k, v)]
+    want = (torch.softmax(t[0] @ t[1].transpose(2, 3).contiguous() * scale, -1) @ t[2]).permute(0, 2, 1, 3)
+    out = torch.empty_like(q)
+    bclib.attention(q, k, v, out, prescaled=prescaled)
+    torch.cuda.synchronize()
+    err = float((out.double() - want).norm() / want.norm())
+    assert err <= 1e-2, err      # probabilities and outputs rounded to bf16 (about 3e-3 together)
