@@ -357,16 +357,12 @@ __device__ __forceinline__ void gemm_dma_body(GemmArgs g, const GemmSeg* sg) {
 }
 
 // ---------------------------------------------------------------------------
-// Wide-tile bf16 kernel for one-round grids.
+// Wide-tile bf16 kernel (128 x 432 and 128 x 128 tiles).
 //
-// Same direct-to-LDS staging and swizzle as above, with three changes:
-//  * tiles need not be powers of two (e.g. 256 x 288 or 128 x 432, so that
-//    the DiT-XL/2 and PixArt block GEMMs split into exactly 256 tiles or a
-//    whole number of rounds over the 256 CUs); the (BM + BN) / 8 row octets
-//    of a k-step are dealt round-robin to the waves, which need not get equal
-//    counts (the pipeline waits count each wave's own loads);
-//  * a wave owns a 64 x 144 (or 64 x 128) block, halving the LDS bytes read
-//    per MFMA flop relative to 32 x 64;
+// Same direct-to-LDS staging and swizzle as above, two stages, with two
+// changes:
+//  * tiles need not be powers of two (128 x 432); the (BM + BN) / 8 row octets
+//    of a k-step are dealt round-robin to the waves;
 //  * the MFMA operands are swapped (W rows as the instruction's A), so lane l
 //    accumulates out[row][col..col+3] with row = l % 16 and
 //    col = 4 (l / 16): the epilogue reads and writes four consecutive
@@ -384,42 +380,30 @@ __device__ __forceinline__ void st4(float* p, const float (&v)[4]) {
     *reinterpret_cast<f32x4*>(p) = f32x4{v[0], v[1], v[2], v[3]};
 }
 
-// Residual of the gated-residual epilogue, loaded into registers at the start
-// of the last k-step so that its latency hides behind the MFMAs, when a wave's
-// share is small enough to sit beside the accumulators (at most 12 MFMA tiles);
-// larger tiles read it in the epilogue.  The gate (one row per sample) is read
-// in the epilogue from cache.
-template <int EPI, int TM, int TN> struct EpiPrefetch {
-    static constexpr bool early = EPI == BC_EPI_GATE_RES && TM * TN <= 12;
-    f32x4 res[early ? TM : 1][early ? TN : 1];
-    __device__ __forceinline__ void load(const GemmArgs& g, int row0, int col0, int lane, int jn) {
-        if constexpr (early) {
-            const GemmEpi& e = g.e;
+// The gated residual of four consecutive columns of one row (bf16 operands).
+__device__ __forceinline__ void gate_res4(const GemmArgs& g, int row, int col, const f32x4& acc, const f32x4& res) {
+    const GemmEpi& e = g.e;
+    const int b = row / e.seg, sidx = row - b * e.seg;
+    if (sidx >= e.keep) return;
+    const f32x4 gv = e.gate ? *reinterpret_cast<const f32x4*>(e.gate + (int64_t)(row / e.rows_per_gate) * e.ldg + col)
+                            : f32x4{1.f, 1.f, 1.f, 1.f};
+    float bv[4] = {0.f, 0.f, 0.f, 0.f}, v[4];
+    if (e.bias) {
+        const bf16x4 b4 = *reinterpret_cast<const bf16x4*>(static_cast<const bf16*>(e.bias) + col);
 #pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int row = min(row0 + i * 16 + (lane & 15), g.M - 1);
-                const float* rrow = e.res + (int64_t)row * e.ldr;
+        for (int r = 0; r < 4; ++r) bv[r] = (float)b4[r];
+    }
 #pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    if (j >= jn) break;
-                    const int col = min(col0 + j * 16 + 4 * (lane >> 4), g.N - 4);
-                    res[i][j] = *reinterpret_cast<const f32x4*>(rrow + col);
-                }
-            }
-        }
-    }
-    __device__ __forceinline__ f32x4 get(const GemmArgs& g, int i, int j, int row, int col) const {
-        if constexpr (early) return res[i][j];
-        else return *reinterpret_cast<const f32x4*>(g.e.res + (int64_t)row * g.e.ldr + col);
-    }
-};
+    for (int r = 0; r < 4; ++r) v[r] = res[r] + gv[r] * (acc[r] + bv[r]);
+    const int64_t o = (int64_t)(b * e.keep + sidx) * e.ldo + col;
+    if (e.out_f32) st4(static_cast<float*>(e.out) + o, v);
+    else st4(static_cast<bf16*>(e.out) + o, v);
+}
 
 // Epilogue straight from the accumulators (gated residual; fp32 outputs of
-// the plain epilogue).  jn: number of the TN column blocks this wave holds.
-
+// the plain epilogue).
 template <int EPI, int TM, int TN>
-__device__ __forceinline__ void epilogue_t(const GemmArgs& g, const f32x4 (&acc)[TM][TN], int row0, int col0, int lane,
-                                           int jn, const EpiPrefetch<EPI, TM, TN>& pf) {
+__device__ __forceinline__ void epilogue_t(const GemmArgs& g, const f32x4 (&acc)[TM][TN], int row0, int col0, int lane) {
     const GemmEpi& e = g.e;
     if constexpr (EPI == BC_EPI_GATE_RES) {
         // Rows outer: the row's destination (ring-slot remap) is worked out once.
@@ -433,7 +417,6 @@ __device__ __forceinline__ void epilogue_t(const GemmArgs& g, const f32x4 (&acc)
             const float* grow = e.gate ? e.gate + (int64_t)(row / e.rows_per_gate) * e.ldg : nullptr;
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                if (j >= jn) break;
                 const int col = col0 + j * 16 + 4 * (lane >> 4);
                 if (col >= g.N) continue;
                 float v[4];
@@ -445,7 +428,7 @@ __device__ __forceinline__ void epilogue_t(const GemmArgs& g, const f32x4 (&acc)
                     for (int r = 0; r < 4; ++r) bv[r] = (float)b4[r];
                 }
                 const f32x4 gv = grow ? *reinterpret_cast<const f32x4*>(grow + col) : f32x4{1.f, 1.f, 1.f, 1.f};
-                const f32x4 rv = pf.get(g, i, j, row, col);
+                const f32x4 rv = *reinterpret_cast<const f32x4*>(e.res + (int64_t)row * e.ldr + col);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) v[r] = rv[r] + gv[r] * (acc[i][j][r] + bv[r]);
                 if (e.out_f32) st4(static_cast<float*>(e.out) + orow + col, v);
@@ -455,10 +438,8 @@ __device__ __forceinline__ void epilogue_t(const GemmArgs& g, const f32x4 (&acc)
         return;
     }
     const bf16* __restrict__ bias = static_cast<const bf16*>(e.bias);
-    const bool odd = (lane >> 4) & 1;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-        if (j >= jn) break;
         const int col = col0 + j * 16 + 4 * (lane >> 4);
         const bool col_ok = col < g.N;
         float bv[4] = {0.f, 0.f, 0.f, 0.f};
@@ -490,21 +471,6 @@ __device__ __forceinline__ void epilogue_t(const GemmArgs& g, const f32x4 (&acc)
     }
 }
 
-// LDS slot of 16-byte chunk c in row r for k-steps of BK = 64 (128-byte rows,
-// 8 chunks) or BK = 32 (64-byte rows, 4 chunks): the 16 rows read by one
-// fragment load fall on 16 distinct 16-byte bank groups.
-template <int BK> __device__ __forceinline__ int wslot(int c, int r) {
-    if constexpr (BK == 64) return c ^ ((r >> 1) & 7);
-    else return c ^ ((r >> 2) & 3);
-}
-
-// KG > 1: split K inside the workgroup.  KG groups of WAVES_M x WAVES_N waves
-// share the tile; a stage holds KG consecutive 64-wide k-blocks (one per
-// group, each laid out as above), so every wave keeps a full accumulator over
-// 1/KG of K.  The groups' partial tiles are then summed through LDS and group
-// 0 applies the epilogue.  (For small outputs: 128 x 144 tiles of 2 x 2 waves
-// of 64 x 80 / 64 x 64 in two groups keep eight waves per CU with large wave
-// tiles where a one-round grid has only 256 tiles.)
 // Wait until at most `later` groups of Q direct-to-LDS loads (issued after the
 // group waited for) are outstanding; `later` >= LMAX waits for all.
 template <int Q, int L = 0, int LMAX = 3> __device__ __forceinline__ void wait_groups(int later) {
@@ -519,42 +485,29 @@ template <int Q, int L = 0, int LMAX = 3> __device__ __forceinline__ void wait_g
     }
 }
 
-template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int BK, int KG, int PIPE>
-__device__ __forceinline__ void gemm_wide_body(GemmArgs g, int tile) {
+template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_wide_kernel(GemmArgs g) {
     typedef bf16 T;
     typedef Mma<bf16> MM;
-    constexpr int NWG = WAVES_M * WAVES_N;                // waves per K group
-    constexpr int NW = NWG * KG;
-    static_assert(BK == 64 || BK == 32, "k-step");
-    static_assert(KG == 1 || KG == 2, "K groups");
-    constexpr int CPR = BK / 8;                            // 16-byte chunks per LDS row
-    constexpr int RPI = 64 / CPR;                          // rows per wave-wide load
-    constexpr int WM = BM / WAVES_M, TM = WM / 16;
-    // The BN / 16 column blocks are dealt to the WAVES_N wave columns as
-    // evenly as possible (144 = 80 + 64 for two): TN is the larger share.
-    constexpr int NBLK = BN / 16, TN = (NBLK + WAVES_N - 1) / WAVES_N, NREM = NBLK % WAVES_N;
-    constexpr int GOCT = (BM + BN) / RPI;                  // wave-wide loads per group block
-    constexpr int NOCT = GOCT * KG;                        // wave-wide loads per stage
-    constexpr int QMAX = (NOCT + NW - 1) / NW;             // octets per wave (at most)
-    static_assert(TM * 16 * WAVES_M == BM && BM % 16 == 0 && BN % 16 == 0, "tile shape");
-    constexpr int GBLK = (BM + BN) * BK;                   // elements per group block: BM rows of A, then BN rows of W
-    constexpr int STAGE = GBLK * KG;
+    constexpr int NW = WAVES_M * WAVES_N, NT = 64 * NW, BK = 64;
+    constexpr int TM = BM / WAVES_M / 16, TN = BN / WAVES_N / 16;
+    constexpr int NOCT = (BM + BN) / 8;                    // wave-wide loads per stage (8 rows of 128 bytes each)
+    constexpr int QMAX = (NOCT + NW - 1) / NW;             // of them per wave (at most)
+    static_assert(TM * 16 * WAVES_M == BM && TN * 16 * WAVES_N == BN, "tile shape");
+    constexpr int STAGE = (BM + BN) * BK;                  // BM rows of A, then BN rows of W
     constexpr int OPITCH = BN + 8;                         // staged bf16 output row (16-byte pad)
-    constexpr int SMEM0 = STAGES * STAGE > BM * OPITCH ? STAGES * STAGE : BM * OPITCH;
+    constexpr int SMEM0 = 2 * STAGE > BM * OPITCH ? 2 * STAGE : BM * OPITCH;
     // Gated epilogue through LDS (small tiles): an fp32 row-major copy of the
     // tile, FPITCH floats per row.
     constexpr int FPITCH = BN + 4;
     constexpr bool STAGE_GATED = EPI == BC_EPI_GATE_RES && BM * FPITCH * 4 <= 96 * 1024;
-    constexpr int RED = STAGE_GATED ? BM * FPITCH * 2 : KG > 1 ? NWG * TM * TN * 64 * 4 * 2 : 0;   // in bf16 units
-    constexpr int SMEM = SMEM0 > RED ? SMEM0 : RED;
+    constexpr int SMEM = STAGE_GATED && BM * FPITCH * 2 > SMEM0 ? BM * FPITCH * 2 : SMEM0;   // in bf16 units
     __shared__ __attribute__((aligned(1024))) T sm[SMEM];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kg = wave / NWG, wig = wave % NWG;
-    const int wm = wig / WAVES_N, wn = wig % WAVES_N;
-    const int jn = NREM == 0 ? TN : NBLK / WAVES_N + (wn < NREM ? 1 : 0);    // this wave's column blocks
-    const int j0 = NREM == 0 ? wn * TN : wn * (NBLK / WAVES_N) + min(wn, NREM);
+    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    const int tile = xcd_contiguous(blockIdx.x, gridDim.x);
 
     const int tiles_m = (g.M + BM - 1) / BM;
     const int tiles_n = (g.N + BN - 1) / BN;
@@ -566,28 +519,24 @@ __device__ __forceinline__ void gemm_wide_body(GemmArgs g, int tile) {
     const int tn = (tile % group) / gm;
     const int bm = tm * BM, bn = tn * BN;
 
-    // Load o = wave + NW q of a stage fills rows RPI (o % GOCT) .. + RPI - 1 of
-    // group block o / GOCT (A rows first, then W rows); lane L loads row
-    // RPI (o % GOCT) + L / CPR into slot L % CPR, fetching the global chunk
-    // that the swizzle puts there.
+    // Load o = wave + NW q of a stage fills rows 8 o .. 8 o + 7 (A rows first,
+    // then W rows); lane L loads row 8 o + L / 8 into slot L % 8, fetching the
+    // global chunk that the swizzle puts there.
     const T* src[QMAX];
-    const int lrow = lane / CPR, lslot = lane % CPR;
 #pragma unroll
     for (int q = 0; q < QMAX; ++q) {
-        const int o = min(wave + NW * q, NOCT - 1);
-        const int og = o / GOCT, r = RPI * (o % GOCT) + lrow;
+        const int r = 8 * min(wave + NW * q, NOCT - 1) + (lane >> 3);
         const T* p;
         if (r < BM) p = static_cast<const T*>(g.A) + (int64_t)min(bm + r, g.M - 1) * g.lda;
         else p = static_cast<const T*>(g.W) + (int64_t)min(bn + r - BM, g.N - 1) * g.ldw;
-        src[q] = p + og * BK + wslot<BK>(lslot, r) * 8;
+        src[q] = p + ((lane & 7) ^ swz(r)) * 8;
     }
-    const int nk = g.K / (BK * KG);                        // stages
+    const int nk = g.K / BK;
     auto issue = [&](int kt, int buf) {
-        const int k0 = kt * BK * KG;
 #pragma unroll
         for (int q = 0; q < QMAX; ++q) {
             const int o = wave + NW * q;
-            if (NOCT % NW == 0 || o < NOCT) dma16(src[q] + k0, &sm[buf * STAGE + (o / GOCT) * GBLK + (o % GOCT) * RPI * BK]);
+            if (NOCT % NW == 0 || o < NOCT) dma16(src[q] + kt * BK, &sm[buf * STAGE + o * 8 * BK]);
         }
     };
 
@@ -597,202 +546,78 @@ __device__ __forceinline__ void gemm_wide_body(GemmArgs g, int tile) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    EpiPrefetch<EPI, TM, TN> pf;
-#pragma unroll
-    for (int p = 0; p < STAGES - 1; ++p)
-        if (p < nk) issue(p, p);
-    // Loads this wave issues per k-step (waves below NOCT % NW get one more).
-    const bool more = NOCT % NW == 0 || wave < NOCT % NW;
+    issue(0, 0);
     const int frow = lane & 15, grp = lane >> 4;
-    if constexpr (PIPE) {
-        // Software-pipelined k loop: the barrier sits between the two 32-wide
-        // halves of a k-step, so the fragments of the next step's first half
-        // are read from LDS while this step's second-half MFMAs run, and the
-        // second half's fragments while the first half's run.  Stage kt's
-        // buffer is last read before the middle barrier of step kt, so the
-        // loads of step kt + STAGES - 1 may overwrite it at the top of kt + 1.
-        static_assert(KG == 1 && BK == 64 && STAGES >= 3 && STAGES <= 5, "pipelined k loop");
-        // Fragments live across the loop as 32-bit words (a bf16 vector
-        // carried around the loop is split into halves and re-packed with
-        // byte permutes, which makes the MFMAs wait on the next reads).
-        u32x4 fa[2][TM], fb[2][TN];
-        auto read = [&](int kt, int kk, u32x4 (&a)[TM], u32x4 (&b)[TN]) {
-            const T* st = sm + (kt % STAGES) * STAGE;
-            const int c = kk * 4 + grp;
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int r = wm * WM + i * 16 + frow;
-                a[i] = *reinterpret_cast<const u32x4*>(st + r * BK + wslot<BK>(c, r) * 8);
-            }
-            // Waves with the smaller column share read their last block twice
-            // rather than leaving a fragment conditionally unset.
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int r = BM + (j0 + (NREM != 0 && j >= jn ? jn - 1 : j)) * 16 + frow;
-                b[j] = *reinterpret_cast<const u32x4*>(st + r * BK + wslot<BK>(c, r) * 8);
-            }
-        };
-        // Unconditional: the accumulators past a wave's share (j >= jn) take
-        // the duplicated block and are never stored; branch-free issue.
-        auto mma = [&](const u32x4 (&a)[TM], const u32x4 (&b)[TN]) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = MM::mma(__builtin_bit_cast(MM::frag, b[j]), __builtin_bit_cast(MM::frag, a[i]), acc[i][j]);
-        };
-        // Stage j's loads are done once at most (loads issued after them) are
-        // outstanding: min(STAGES - 2, nk - 1 - j) groups of QMAX (or QMAX - 1).
-        auto wait_stage = [&](int j) {
-            const int later = min(STAGES - 2, nk - 1 - j);
-            if (more) wait_groups<QMAX, 0, STAGES - 1>(later);
-            else wait_groups<QMAX - 1, 0, STAGES - 1>(later);
-        };
-        wait_stage(0);
-        __syncthreads();
-        read(0, 0, fa[0], fb[0]);
-        // All but the last step; the last one (no next stage) is peeled so
-        // that no control-flow merge sits between a step's second-half reads
-        // and its MFMAs (the merged wait counts would make them wait).
-        // In each half the fragment reads are issued first, ahead of the
-        // MFMAs on the other buffer, so their latency hides behind them.
-        for (int kt = 0; kt + 1 < nk; ++kt) {
-            if (kt + STAGES - 1 < nk) issue(kt + STAGES - 1, (kt + STAGES - 1) % STAGES);
-            __builtin_amdgcn_sched_barrier(0);
-            read(kt, 1, fa[1], fb[1]);
-            mma(fa[0], fb[0]);
-            __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);   // DS reads
-            __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);   // MFMAs
-            wait_stage(kt + 1);
-            __syncthreads();
-            __builtin_amdgcn_sched_barrier(0);
-            read(kt + 1, 0, fa[0], fb[0]);
-            mma(fa[1], fb[1]);
-            __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);
-        }
-        if (EPI == BC_EPI_GATE_RES && !STAGE_GATED) pf.load(g, bm + wm * WM, bn + j0 * 16, lane, jn);
-        read(nk - 1, 1, fa[1], fb[1]);
-        mma(fa[0], fb[0]);
-        mma(fa[1], fb[1]);
-    } else
     for (int kt = 0; kt < nk; ++kt) {
-        if (STAGES > 2 && kt + STAGES - 2 < nk) {
-            if (more) wait_vmcnt<(STAGES - 2) * QMAX>();
-            else wait_vmcnt<(STAGES - 2) * (QMAX - 1)>();
-        } else {
-            wait_vmcnt<0>();
-        }
+        wait_vmcnt<0>();
         __syncthreads();
-        if (kt + STAGES - 1 < nk) issue(kt + STAGES - 1, (kt + STAGES - 1) % STAGES);
-        if (EPI == BC_EPI_GATE_RES && !STAGE_GATED && kg == 0 && kt == nk - 1) pf.load(g, bm + wm * WM, bn + j0 * 16, lane, jn);
-        const T* st = sm + (kt % STAGES) * STAGE + kg * GBLK;
+        if (kt + 1 < nk) issue(kt + 1, (kt + 1) & 1);
+        const T* st = sm + (kt & 1) * STAGE;
 #pragma unroll
-        for (int kk = 0; kk < BK / 32; ++kk) {
+        for (int kk = 0; kk < 2; ++kk) {
             const int c = kk * 4 + grp;
             MM::frag af[TM], bfr[TN];
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
-                const int r = wm * WM + i * 16 + frow;
-                af[i] = MM::load(st + r * BK + wslot<BK>(c, r) * 8);
+                const int r = (wm * TM + i) * 16 + frow;
+                af[i] = MM::load(st + r * BK + (c ^ swz(r)) * 8);
             }
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                if (NREM != 0 && j >= jn) break;
-                const int r = BM + (j0 + j) * 16 + frow;
-                bfr[j] = MM::load(st + r * BK + wslot<BK>(c, r) * 8);
+                const int r = BM + (wn * TN + j) * 16 + frow;
+                bfr[j] = MM::load(st + r * BK + (c ^ swz(r)) * 8);
             }
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    if (NREM == 0 || j < jn) acc[i][j] = MM::mma(bfr[j], af[i], acc[i][j]);
+                for (int j = 0; j < TN; ++j) acc[i][j] = MM::mma(bfr[j], af[i], acc[i][j]);
         }
     }
 
+    const GemmEpi& e = g.e;
+    const bf16* __restrict__ bias = static_cast<const bf16*>(e.bias);
     if constexpr (STAGE_GATED) {
-        // The tile goes through LDS as fp32 rows (group 1's partial first, then
-        // group 0 adds its own: a fixed order), and all waves then apply the
+        // The tile goes through LDS as fp32 rows, and all waves then apply the
         // gated residual to whole rows, reading the residual and gate and
-        // writing the stream as consecutive 16-byte chunks.
-        const GemmEpi& e = g.e;
+        // writing the stream as consecutive 16-byte chunks.  All of a thread's
+        // residual is requested first: the stream is updated in place, so no
+        // load is moved over a store by itself.
+        constexpr int C4 = BN / 4, IT = BM * C4 / NT;         // 4-column chunks per tile row, and per thread
+        static_assert(IT * NT == BM * C4, "chunks per thread");
+        f32x4 rv[IT];
+#pragma unroll
+        for (int t = 0; t < IT; ++t) {
+            const int q = tid + NT * t, row = min(bm + q / C4, g.M - 1), col = min(bn + q % C4 * 4, g.N - 4);
+            rv[t] = *reinterpret_cast<const f32x4*>(e.res + (int64_t)row * e.ldr + col);
+        }
         float* ft = reinterpret_cast<float*>(sm);
         __syncthreads();   // every wave is done with the stage buffers
-        for (int pass = KG - 1; pass >= 0; --pass) {
-            if (kg == pass) {
 #pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    if (j >= jn) break;
-                    const int lc = (j0 + j) * 16 + 4 * (lane >> 4);
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-                    for (int i = 0; i < TM; ++i) {
-                        f32x4* dst = reinterpret_cast<f32x4*>(ft + (wm * WM + i * 16 + (lane & 15)) * FPITCH + lc);
-                        *dst = pass == KG - 1 ? acc[i][j] : *dst + acc[i][j];
-                    }
-                }
-            }
-            __syncthreads();
-        }
-        const bf16* __restrict__ bias = static_cast<const bf16*>(e.bias);
-        constexpr int NT = 64 * NW, C4 = BN / 4;              // threads; 4-column chunks per tile row
-        for (int q = tid; q < BM * C4; q += NT) {
-            const int lr = q / C4, c4 = q - lr * C4;
-            const int row = bm + lr, col = bn + c4 * 4;
-            if (row >= g.M || col >= g.N) continue;
-            const int b = row / e.seg, sidx = row - b * e.seg;
-            if (sidx >= e.keep) continue;
-            const f32x4 y = *reinterpret_cast<const f32x4*>(ft + lr * FPITCH + c4 * 4);
-            const f32x4 rv = *reinterpret_cast<const f32x4*>(e.res + (int64_t)row * e.ldr + col);
-            const f32x4 gv = e.gate ? *reinterpret_cast<const f32x4*>(e.gate + (int64_t)(row / e.rows_per_gate) * e.ldg + col)
-                                    : f32x4{1.f, 1.f, 1.f, 1.f};
-            float bv[4] = {0.f, 0.f, 0.f, 0.f};
-            if (bias) {
-                const bf16x4 b4 = *reinterpret_cast<const bf16x4*>(bias + col);
+            for (int i = 0; i < TM; ++i)
+                *reinterpret_cast<f32x4*>(ft + ((wm * TM + i) * 16 + frow) * FPITCH + (wn * TN + j) * 16 + 4 * grp) = acc[i][j];
+        __syncthreads();
 #pragma unroll
-                for (int r = 0; r < 4; ++r) bv[r] = (float)b4[r];
-            }
-            float v[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = rv[r] + gv[r] * (y[r] + bv[r]);
-            const int64_t o = (int64_t)(b * e.keep + sidx) * e.ldo + col;
-            if (e.out_f32) st4(static_cast<float*>(e.out) + o, v);
-            else st4(static_cast<bf16*>(e.out) + o, v);
+        for (int t = 0; t < IT; ++t) {
+            const int q = tid + NT * t, lr = q / C4, lc = q % C4 * 4;
+            if (bm + lr < g.M && bn + lc < g.N)
+                gate_res4(g, bm + lr, bn + lc, *reinterpret_cast<const f32x4*>(ft + lr * FPITCH + lc), rv[t]);
         }
         return;
     }
-    if constexpr (KG == 2) {
-        // Group 1 hands its partial tile to group 0 through LDS.
-        __syncthreads();   // every wave is done with the stage buffers
-        f32x4* red = reinterpret_cast<f32x4*>(sm) + wig * TM * TN * 64 + lane;
-        if (kg == 1) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) red[(i * TN + j) * 64] = acc[i][j];
-        }
-        __syncthreads();
-        if (kg == 0) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] += red[(i * TN + j) * 64];
-        }
-    }
     if constexpr (EPI == BC_EPI_BIAS) {
-        if (!g.e.out_f32) {
+        if (!e.out_f32) {
             // bf16 outputs leave through LDS: the waves write their finished
             // values into a row-major copy of the tile, then the workgroup stores
             // it as consecutive 16-byte chunks of each row, so every store
             // instruction covers whole cache lines.  (Written straight from the
             // accumulators, 32-byte pieces of lines from all 256 one-round tiles
             // at once came back as about 1.5x the output bytes in HBM writes.)
-            const GemmEpi& e = g.e;
-            const bf16* __restrict__ bias = static_cast<const bf16*>(e.bias);
-            __syncthreads();   // every wave is done with the stage buffers (and the reduction)
+            __syncthreads();   // every wave is done with the stage buffers
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                if (j >= jn || kg != 0) break;
-                const int lc = (j0 + j) * 16 + 4 * (lane >> 4);
+                const int lc = (wn * TN + j) * 16 + 4 * grp;
                 const int col = bn + lc;
                 float bv[4] = {0.f, 0.f, 0.f, 0.f};
                 if (bias && col < g.N) {
@@ -811,12 +636,11 @@ __device__ __forceinline__ void gemm_wide_body(GemmArgs g, int tile) {
                         if (act) v = gelu_tanh(v);
                         q[r] = (bf16)v;
                     }
-                    const int lr = wm * WM + i * 16 + (lane & 15);
-                    *reinterpret_cast<bf16x4*>(sm + lr * OPITCH + lc) = q;
+                    *reinterpret_cast<bf16x4*>(sm + ((wm * TM + i) * 16 + frow) * OPITCH + lc) = q;
                 }
             }
             __syncthreads();
-            constexpr int NT = 64 * NW, CPRO = BN / 8;    // threads; 16-byte chunks per tile row
+            constexpr int CPRO = BN / 8;    // 16-byte chunks per tile row
             for (int q = tid; q < BM * CPRO; q += NT) {
                 const int lr = q / CPRO, c8 = q - lr * CPRO;
                 const int row = bm + lr, col = bn + c8 * 8;
@@ -829,8 +653,7 @@ __device__ __forceinline__ void gemm_wide_body(GemmArgs g, int tile) {
             return;
         }
     }
-    if (kg != 0) return;
-    epilogue_t<EPI, TM, TN>(g, acc, bm + wm * WM, bn + j0 * 16, lane, jn, pf);
+    epilogue_t<EPI, TM, TN>(g, acc, bm + wm * TM * 16, bn + wn * TN * 16, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1250,16 +1073,10 @@ static void launch_phase(const GemmArgs& g, hipStream_t s) {
     launch_k(gemm_phase_kernel<EPI, NP>, dim3((unsigned)(((g.M + 255) / 256) * ((g.N + BN - 1) / BN))), dim3(512), s, g);
 }
 
-template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int BK, int KG, int PIPE = 0>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void gemm_wide_kernel(GemmArgs g) {
-    gemm_wide_body<EPI, BM, BN, WAVES_M, WAVES_N, STAGES, BK, KG, PIPE>(g, xcd_contiguous(blockIdx.x, gridDim.x));
-}
-
-template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES = 2, int BK = 64, int KG = 1, int PIPE = 0>
+template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N>
 static void launch_wide(const GemmArgs& g, hipStream_t s) {
     const unsigned tiles = (unsigned)(((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN));
-    launch_k(gemm_wide_kernel<EPI, BM, BN, WAVES_M, WAVES_N, STAGES, BK, KG, PIPE>, dim3(tiles),
-             dim3(64 * WAVES_M * WAVES_N * KG), s, g);
+    launch_k(gemm_wide_kernel<EPI, BM, BN, WAVES_M, WAVES_N>, dim3(tiles), dim3(64 * WAVES_M * WAVES_N), s, g);
 }
 
 template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int SW = 0>
@@ -1485,6 +1302,181 @@ static bool vec4_ok(const GemmArgs& g, int epi) {
     return e.split >= g.N || (e.split % 4 == 0 && e.off2 % 4 == 0 && e.ldo2 % 4 == 0 && al(e.out2));
 }
 
+// ---------------------------------------------------------------------------
+// 128 x 144 tiles for grids of at most one round (the N = 1152 projections at
+// M = 4096).
+//
+// What bounds these shapes is what a CU can load (35 KB a k-step at about 64
+// GB/s) and read back from LDS: 16 waves of 32 x 48 and 32 x 32 read 139 KB of
+// fragments a step for 576 cycles of MFMAs.  Here twelve waves, three per SIMD,
+// are two groups of 2 x 3 waves of 64 x 48, each group taking one half of every
+// k-step: 86 KB of fragments a step, read one step ahead of their MFMAs, four
+// stages of loads, one barrier a step; the groups' halves meet in LDS at the
+// end.  M = 4096, N = 1152, K = 4608, gated: 58.1 us with the sixteen waves,
+// 48.9 now (M = 2048: 49.6 and 39.1); K = 1152: 21.1 and 20.0.
+// ---------------------------------------------------------------------------
+template <int EPI>
+__global__ __launch_bounds__(768) void gemm_mid_kernel(GemmArgs g) {
+    typedef Mma<bf16> MM;
+    constexpr int BM = 128, BN = 144, STAGE = (BM + BN) * 128, S = 4;
+    constexpr int TM = 4, TN = 3, NW = 12, NOCT = (BM + BN) / 8, Q = (NOCT + NW - 1) / NW;   // Q: loads per wave and step (at most)
+    constexpr int PITCH = BN + 4;
+    static_assert(BM * PITCH * 4 <= S * STAGE, "the reduced tile fits the stages");
+    __shared__ __attribute__((aligned(1024))) char sm[S * STAGE];
+    typedef __attribute__((address_space(3))) const char lds_char;
+    typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = wave / 6, wig = wave % 6, wm = wig / 3, wn = wig % 3;
+    const int frow = lane & 15, grp = lane >> 4;
+    const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+    const int tile = xcd_contiguous(blockIdx.x, gridDim.x);
+    constexpr int GROUP_M = 8;
+    const int group = GROUP_M * tiles_n;
+    const int first_m = (tile / group) * GROUP_M;
+    const int gm = min(tiles_m - first_m, GROUP_M);
+    const int bm = (first_m + (tile % group) % gm) * BM, bn = (tile % group) / gm * BN;
+
+    const char* baseA = reinterpret_cast<const char*>(static_cast<const bf16*>(g.A) + (int64_t)bm * g.lda);
+    const char* baseW = reinterpret_cast<const char*>(static_cast<const bf16*>(g.W) + (int64_t)bn * g.ldw);
+    // Load o = wave + 12 q of a step fills rows 8 o .. 8 o + 7 of the stage (A rows, then W rows).
+    const bool more = NOCT % NW == 0 || wave < NOCT % NW;
+    uint32_t off[Q];
+    const char* base[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int o = min(wave + NW * q, NOCT - 1), r = 8 * o + (lane >> 3);
+        const uint32_t ch = ((lane & 7) ^ ((r >> 1) & 7)) * 16;
+        base[q] = 8 * o < BM ? baseA : baseW;
+        off[q] = 8 * o < BM ? (uint32_t)(min(bm + r, g.M - 1) - bm) * (uint32_t)(g.lda * 2) + ch
+                            : (uint32_t)(min(bn + r - BM, g.N - 1) - bn) * (uint32_t)(g.ldw * 2) + ch;
+    }
+    const uint32_t ldsw = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_char*)sm + wave * 1024);
+    auto issue = [&](int k, int st) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (q + 1 < Q || more) dma16s(base[q] + (int64_t)k * 128, off[q], ldsw + st * STAGE + q * NW * 1024);
+    };
+    auto wait1 = [&](int later) __attribute__((always_inline)) {      // at most `later` (0 or 1) steps' loads outstanding
+        if (later == 0) wait_vmcnt<0>();
+        else if (more) wait_vmcnt<Q>();
+        else wait_vmcnt<Q - 1>();
+    };
+    const uint32_t c = (uint32_t)((kg * 4 + grp) ^ ((frow >> 1) & 7)) * 16;
+    lds_char* pA = (lds_char*)sm + (wm * 64 + frow) * 128 + c;
+    lds_char* pW = (lds_char*)sm + (BM + wn * 48 + frow) * 128 + c;
+    u32x4 fa[2][TM], fw[2][TN];
+    auto read = [&](int st, int set) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fw[set][j] = *(lds_u32x4*)(pW + st * STAGE + j * 2048);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[set][i] = *(lds_u32x4*)(pA + st * STAGE + i * 2048);
+    };
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto mma = [&](int set) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                acc[i][j] = MM::mma(__builtin_bit_cast(MM::frag, fw[set][j]), __builtin_bit_cast(MM::frag, fa[set][i]), acc[i][j]);
+    };
+    auto barrier = [&]() __attribute__((always_inline)) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const int nk = g.K / 64;
+    // Step k, in stage ST: its fragments are in register set ST & 1.  After the
+    // barrier step k + 1 has landed for every wave, and every wave is done with
+    // the fragments of step k - 1, whose stage step k + 3 takes.
+    auto step = [&](int k, auto stc) __attribute__((always_inline)) {
+        constexpr int ST = decltype(stc)::value;
+        if (k + 1 >= nk) {
+            mma(ST & 1);
+            return;
+        }
+        wait1(k + 2 < nk ? 1 : 0);
+        barrier();
+        if (k + 3 < nk) issue(k + 3, (ST + 3) % 4);
+        read((ST + 1) % 4, (ST + 1) & 1);
+        mma(ST & 1);
+#pragma unroll
+        for (int z = 0; z < TM + TN; ++z) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - TM - TN, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+        if (p < nk) issue(p, p);
+    if (nk > 2) { if (more) wait_vmcnt<2 * Q>(); else wait_vmcnt<2 * (Q - 1)>(); }
+    else wait1(nk > 1 ? 1 : 0);
+    barrier();
+    read(0, 0);
+    int k = 0;
+    for (; k + 4 <= nk; k += 4) {
+        step(k, std::integral_constant<int, 0>{});
+        step(k + 1, std::integral_constant<int, 1>{});
+        step(k + 2, std::integral_constant<int, 2>{});
+        step(k + 3, std::integral_constant<int, 3>{});
+    }
+    if (k < nk) step(k, std::integral_constant<int, 0>{});
+    if (k + 1 < nk) step(k + 1, std::integral_constant<int, 1>{});
+    if (k + 2 < nk) step(k + 2, std::integral_constant<int, 2>{});
+
+    // The residual is on its way while the two groups' halves meet in LDS (group
+    // 1's first, then group 0 adds its own); all waves then finish whole rows.
+    constexpr int C4 = BN / 4, IT = BM * C4 / 768;
+    static_assert(IT * 768 == BM * C4, "chunks per thread");
+    f32x4 rv[EPI == BC_EPI_GATE_RES ? IT : 1];
+    if constexpr (EPI == BC_EPI_GATE_RES) {
+#pragma unroll
+        for (int t = 0; t < IT; ++t) {
+            const int q = tid + 768 * t, row = min(bm + q / C4, g.M - 1), col = min(bn + q % C4 * 4, g.N - 4);
+            rv[t] = *reinterpret_cast<const f32x4*>(g.e.res + (int64_t)row * g.e.ldr + col);
+        }
+    }
+    float* ft = reinterpret_cast<float*>(sm);
+    __syncthreads();
+#pragma unroll
+    for (int pass = 1; pass >= 0; --pass) {
+        if (kg == pass) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    f32x4* d = reinterpret_cast<f32x4*>(ft + (wm * 64 + i * 16 + frow) * PITCH + wn * 48 + j * 16 + 4 * grp);
+                    *d = pass == 1 ? acc[i][j] : *d + acc[i][j];
+                }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int t = 0; t < IT; ++t) {
+        const int q = tid + 768 * t, lr = q / C4, lc = q % C4 * 4;
+        const int row = bm + lr, col = bn + lc;
+        if (row >= g.M || col >= g.N) continue;
+        const f32x4 y = *reinterpret_cast<const f32x4*>(ft + lr * PITCH + lc);
+        if constexpr (EPI == BC_EPI_GATE_RES) {
+            gate_res4(g, row, col, y, rv[t]);
+        } else {
+            finish4<bf16, EPI>(g, row, col, y, true);
+        }
+    }
+}
+
+template <int EPI>
+static void launch_mid(const GemmArgs& g, hipStream_t s) {
+    launch_k(gemm_mid_kernel<EPI>, dim3((unsigned)(((g.M + 127) / 128) * ((g.N + 143) / 144))), dim3(768), s, g);
+}
+
 template <typename T, int EPI, int BM, int BN, int WAVES_M, int WAVES_N>
 static void launch_tile(const GemmArgs& g, hipStream_t s) {
     const unsigned tiles = (unsigned)(((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN));
@@ -1530,13 +1522,10 @@ static int phase_parts(const GemmArgs& g) {
 //     kernel;
 //   * N a multiple of 432 with at least one round of 128 x 432 tiles (the
 //     DiT-XL/2 QKV projection: exactly 256): 2 x 4 waves of 64 x 112 / 64 x 96;
-//   * at most 256 tiles of 128 x 144 (the N = 1152 projections at M = 4096):
-//     2 x 4 waves of 64 x 48 / 64 x 32 with four stages in flight (in the
-//     model their weights come cold from HBM every block: 4 stages ran the
-//     DiT-XL/2 sampler 7 % faster than 2) and the gated epilogue staged
-//     through LDS; for the plain epilogue with K % 128 == 0, K split over two
-//     groups of 2 x 2 waves (64 x 80 / 64 x 64) instead;
-//   * otherwise 128 x 128 (8 waves of 32 x 64, two workgroups per CU).
+//   * at most 256 tiles of 128 x 144 (the N = 1152 projections at M = 4096) and
+//     K >= 1024: those (M = 4096, N = 1152, K = 1152: 20.0 us against 24.8
+//     with 128 x 128 tiles; M = 3000, K = 768: 15.0 against 12.6);
+//   * otherwise 128 x 128 (16 waves of 32 x 32, two workgroups per CU).
 // Other bf16 operands take the direct-to-LDS kernel with the scalar
 // epilogue, or the register-staged kernel; fp32 the register-staged kernel.
 // Before all of these, grids too small for them go to the k-split kernel.
@@ -1598,9 +1587,8 @@ static int run_gemm(const GemmArgs& g, hipStream_t s) {
                 launch_phase<EPI, 3>(g, s);
             } else if (g.N % 432 == 0 && (int64_t)((g.M + 127) / 128) * (g.N / 432) >= 256) {
                 launch_wide<EPI, 128, 432, 4, 3>(g, s);
-            } else if (tiles144 <= 256) {
-                if (EPI == BC_EPI_BIAS && g.K % 128 == 0) launch_wide<EPI, 128, 144, 2, 2, 2, 64, 2>(g, s);
-                else launch_wide<EPI, 128, 144, 4, 4, 4, 64, 1, 1>(g, s);
+            } else if (tiles144 <= 256 && g.K >= 1024 && (g.lda > g.ldw ? g.lda : g.ldw) <= (1 << 22)) {
+                launch_mid<EPI>(g, s);
             } else {
                 launch_wide<EPI, 128, 128, 4, 4>(g, s);
             }

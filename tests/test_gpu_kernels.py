@@ -222,3 +222,11 @@ def test_attention_four_waves(bclib, prescaled, B, H, Tq, Tk, d):
     torch.cuda.synchronize()
     err = float((out.double() - want).norm() / want.norm())
     assert err <= 1e-2, err      # probabilities and outputs rounded to bf16 (about 3e-3 together)
+
+
+# The 128 x 144 tiles: ragged rows and columns, every remainder of the k-steps by
+# the four stages.
+@pytest.mark.parametrize("epi", ["bias", "gelu", "gate"])
+@pytest.mark.parametrize("K", [1024, 1088, 1152, 1216])
+def test_linear_one_round(bclib, K, epi):
+    test_linear_small_grids(bclib, "bf16", 3900, 1144, K, 0, epi)
