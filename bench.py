@@ -213,10 +213,10 @@ def group_launches(records, cfg):
 
 # kernel-name prefix of a profiled class's launches (the gated epilogue is template argument 2)
 CLASS_KERNEL = {"attention": ("void bc::attention_dma_kernel<",),
-                "gemm_gated": ("void bc::gemm_wide_kernel<2,", "void bc::gemm_phase_kernel<2,", "void bc::gemm_phase_pair_kernel<2>", "void bc::gemm_mid_kernel<2>"),
-                "gemm_down": ("void bc::gemm_wide_kernel<2,", "void bc::gemm_phase_kernel<2,", "void bc::gemm_phase_pair_kernel<2>", "void bc::gemm_mid_kernel<2>"),
-                "gemm_gelu": ("void bc::gemm_wide_kernel<0,", "void bc::gemm_phase_kernel<0,", "void bc::gemm_phase_pair_kernel<0>", "void bc::gemm_mid_kernel<0>"),
-                "gemm_bias": ("void bc::gemm_wide_kernel<0,", "void bc::gemm_phase_kernel<0,", "void bc::gemm_phase_pair_kernel<0>", "void bc::gemm_mid_kernel<0>")}
+                "gemm_gated": ("void bc::gemm_wide_kernel<2,", "void bc::gemm_phase_kernel<2,", "void bc::gemm_phase_pair_kernel<2>", "void bc::gemm_mid_kernel<2,"),
+                "gemm_down": ("void bc::gemm_wide_kernel<2,", "void bc::gemm_phase_kernel<2,", "void bc::gemm_phase_pair_kernel<2>", "void bc::gemm_mid_kernel<2,"),
+                "gemm_gelu": ("void bc::gemm_wide_kernel<0,", "void bc::gemm_phase_kernel<0,", "void bc::gemm_phase_pair_kernel<0>", "void bc::gemm_mid_kernel<0,"),
+                "gemm_bias": ("void bc::gemm_wide_kernel<0,", "void bc::gemm_phase_kernel<0,", "void bc::gemm_phase_pair_kernel<0>", "void bc::gemm_mid_kernel<0,")}
 
 
 def loop_traffic(workload, g, src):
@@ -255,8 +255,9 @@ def grid_fits(kernel, grid_threads, g):
         if (args[4] == "true") != (Tk > 256):
             return False
         return grid_threads == -(-Tq // qt) * H * B * 64 * nwv
-    if "gemm_mid" in kernel:     # 128 x 144 tiles of 768 threads
-        return grid_threads == -(-g["shape"][0] // 128) * -(-g["shape"][1] // 144) * 768
+    if "gemm_mid" in kernel:     # 128 x 144 (768 threads) or 128 x 192 (1024)
+        bn = int(args[1])
+        return grid_threads == -(-g["shape"][0] // 128) * -(-g["shape"][1] // bn) * 64 * (bn // 12)
     if "gemm_phase" in kernel:   # 256 x 256 (pairs too) or 256 x 288 tiles of 512 threads
         bn = 288 if len(args) > 1 and args[1] == "3" else 256
         return grid_threads == -(-g["shape"][0] // 256) * -(-g["shape"][1] // bn) * 512

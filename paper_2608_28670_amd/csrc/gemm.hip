@@ -1303,23 +1303,25 @@ static bool vec4_ok(const GemmArgs& g, int epi) {
 }
 
 // ---------------------------------------------------------------------------
-// 128 x 144 tiles for grids of at most one round (the N = 1152 projections at
-// M = 4096).
+// 128 x 144 and 128 x 192 tiles for grids of at most one round (the N = 1152
+// projections at M = 4096; the video model's N = 3072 at one frame).
 //
 // What bounds these shapes is what a CU can load (35 KB a k-step at about 64
 // GB/s) and read back from LDS: 16 waves of 32 x 48 and 32 x 32 read 139 KB of
-// fragments a step for 576 cycles of MFMAs.  Here twelve waves, three per SIMD,
-// are two groups of 2 x 3 waves of 64 x 48, each group taking one half of every
-// k-step: 86 KB of fragments a step, read one step ahead of their MFMAs, four
+// fragments a step for 576 cycles of MFMAs.  Here twelve (sixteen) waves, three
+// (four) per SIMD, are two groups of 2 x 3 (2 x 4) waves of 64 x 48, each group
+// taking one half of every k-step: 86 KB of fragments a step, read one step ahead of their MFMAs, four
 // stages of loads, one barrier a step; the groups' halves meet in LDS at the
 // end.  M = 4096, N = 1152, K = 4608, gated: 58.1 us with the sixteen waves,
-// 48.9 now (M = 2048: 49.6 and 39.1); K = 1152: 21.1 and 20.0.
+// 48.9 now (M = 2048: 49.6 and 39.1); K = 1152: 21.1 and 20.0.  128 x 192:
+// M = 1846, N = 3072, K = 15 360, gated: 171 us against 217 with
+// 128 x 128 (two rounds of loads on the CUs that get two); K = 3072: 43 and 50.
 // ---------------------------------------------------------------------------
-template <int EPI>
-__global__ __launch_bounds__(768) void gemm_mid_kernel(GemmArgs g) {
+template <int EPI, int BN>
+__global__ __launch_bounds__(64 * (BN / 12)) void gemm_mid_kernel(GemmArgs g) {
     typedef Mma<bf16> MM;
-    constexpr int BM = 128, BN = 144, STAGE = (BM + BN) * 128, S = 4;
-    constexpr int TM = 4, TN = 3, NW = 12, NOCT = (BM + BN) / 8, Q = (NOCT + NW - 1) / NW;   // Q: loads per wave and step (at most)
+    constexpr int BM = 128, STAGE = (BM + BN) * 128, S = 4;
+    constexpr int TM = 4, TN = 3, WN = BN / 48, NW = 4 * WN, NT = 64 * NW, NOCT = (BM + BN) / 8, Q = (NOCT + NW - 1) / NW;   // Q: loads per wave and step (at most)
     constexpr int PITCH = BN + 4;
     static_assert(BM * PITCH * 4 <= S * STAGE, "the reduced tile fits the stages");
     __shared__ __attribute__((aligned(1024))) char sm[S * STAGE];
@@ -1327,7 +1329,7 @@ __global__ __launch_bounds__(768) void gemm_mid_kernel(GemmArgs g) {
     typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kg = wave / 6, wig = wave % 6, wm = wig / 3, wn = wig % 3;
+    const int kg = wave / (2 * WN), wig = wave % (2 * WN), wm = wig / WN, wn = wig % WN;
     const int frow = lane & 15, grp = lane >> 4;
     const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     const int tile = xcd_contiguous(blockIdx.x, gridDim.x);
@@ -1339,7 +1341,7 @@ __global__ __launch_bounds__(768) void gemm_mid_kernel(GemmArgs g) {
 
     const char* baseA = reinterpret_cast<const char*>(static_cast<const bf16*>(g.A) + (int64_t)bm * g.lda);
     const char* baseW = reinterpret_cast<const char*>(static_cast<const bf16*>(g.W) + (int64_t)bn * g.ldw);
-    // Load o = wave + 12 q of a step fills rows 8 o .. 8 o + 7 of the stage (A rows, then W rows).
+    // Load o = wave + NW q of a step fills rows 8 o .. 8 o + 7 of the stage (A rows, then W rows).
     const bool more = NOCT % NW == 0 || wave < NOCT % NW;
     uint32_t off[Q];
     const char* base[Q];
@@ -1357,15 +1359,17 @@ __global__ __launch_bounds__(768) void gemm_mid_kernel(GemmArgs g) {
         for (int q = 0; q < Q; ++q)
             if (q + 1 < Q || more) dma16s(base[q] + (int64_t)k * 128, off[q], ldsw + st * STAGE + q * NW * 1024);
     };
-    auto wait1 = [&](int later) __attribute__((always_inline)) {      // at most `later` (0 or 1) steps' loads outstanding
-        if (later == 0) wait_vmcnt<0>();
-        else if (more) wait_vmcnt<Q>();
-        else wait_vmcnt<Q - 1>();
+    auto wait_steps = [&](int later) __attribute__((always_inline)) {      // at most `later` (0 to 2) steps' loads outstanding
+        if (more) wait_groups<Q, 0, 3>(later);
+        else wait_groups<Q - 1, 0, 3>(later);
     };
     const uint32_t c = (uint32_t)((kg * 4 + grp) ^ ((frow >> 1) & 7)) * 16;
     lds_char* pA = (lds_char*)sm + (wm * 64 + frow) * 128 + c;
     lds_char* pW = (lds_char*)sm + (BM + wn * 48 + frow) * 128 + c;
-    u32x4 fa[2][TM], fw[2][TN];
+    // Fragments one step ahead of their MFMAs where the registers allow it (three
+    // waves per SIMD; four hide the reads by themselves).
+    constexpr bool AHEAD = NW == 12;
+    u32x4 fa[AHEAD ? 2 : 1][TM], fw[AHEAD ? 2 : 1][TN];
     auto read = [&](int st, int set) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) fw[set][j] = *(lds_u32x4*)(pW + st * STAGE + j * 2048);
@@ -1391,35 +1395,45 @@ __global__ __launch_bounds__(768) void gemm_mid_kernel(GemmArgs g) {
         __builtin_amdgcn_sched_barrier(0);
     };
     const int nk = g.K / 64;
-    // Step k, in stage ST: its fragments are in register set ST & 1.  After the
-    // barrier step k + 1 has landed for every wave, and every wave is done with
-    // the fragments of step k - 1, whose stage step k + 3 takes.
+    // Step k, in stage ST.  After the barrier the step that is read next (k, or k
+    // + 1 when reading ahead) has landed for every wave, and every wave is done
+    // with the fragments of step k - 1, whose stage step k + 3 takes.
     auto step = [&](int k, auto stc) __attribute__((always_inline)) {
         constexpr int ST = decltype(stc)::value;
-        if (k + 1 >= nk) {
+        if constexpr (AHEAD) {
+            if (k + 1 >= nk) {
+                mma(ST & 1);
+                return;
+            }
+            wait_steps(min(1, nk - 2 - k));
+            barrier();
+            if (k + 3 < nk) issue(k + 3, (ST + 3) % 4);
+            read((ST + 1) % 4, (ST + 1) & 1);
             mma(ST & 1);
-            return;
-        }
-        wait1(k + 2 < nk ? 1 : 0);
-        barrier();
-        if (k + 3 < nk) issue(k + 3, (ST + 3) % 4);
-        read((ST + 1) % 4, (ST + 1) & 1);
-        mma(ST & 1);
 #pragma unroll
-        for (int z = 0; z < TM + TN; ++z) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            for (int z = 0; z < TM + TN; ++z) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - TM - TN, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
+            wait_steps(min(2, nk - 1 - k));
+            barrier();
+            if (k + 3 < nk) issue(k + 3, (ST + 3) % 4);
+            read(ST, 0);
+            mma(0);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - TM - TN, 0);
-        __builtin_amdgcn_sched_barrier(0);
     };
 #pragma unroll
     for (int p = 0; p < 3; ++p)
         if (p < nk) issue(p, p);
-    if (nk > 2) { if (more) wait_vmcnt<2 * Q>(); else wait_vmcnt<2 * (Q - 1)>(); }
-    else wait1(nk > 1 ? 1 : 0);
-    barrier();
-    read(0, 0);
+    if constexpr (AHEAD) {
+        wait_steps(min(2, nk - 1));
+        barrier();
+        read(0, 0);
+    }
     int k = 0;
     for (; k + 4 <= nk; k += 4) {
         step(k, std::integral_constant<int, 0>{});
@@ -1433,13 +1447,13 @@ __global__ __launch_bounds__(768) void gemm_mid_kernel(GemmArgs g) {
 
     // The residual is on its way while the two groups' halves meet in LDS (group
     // 1's first, then group 0 adds its own); all waves then finish whole rows.
-    constexpr int C4 = BN / 4, IT = BM * C4 / 768;
-    static_assert(IT * 768 == BM * C4, "chunks per thread");
+    constexpr int C4 = BN / 4, IT = BM * C4 / NT;
+    static_assert(IT * NT == BM * C4, "chunks per thread");
     f32x4 rv[EPI == BC_EPI_GATE_RES ? IT : 1];
     if constexpr (EPI == BC_EPI_GATE_RES) {
 #pragma unroll
         for (int t = 0; t < IT; ++t) {
-            const int q = tid + 768 * t, row = min(bm + q / C4, g.M - 1), col = min(bn + q % C4 * 4, g.N - 4);
+            const int q = tid + NT * t, row = min(bm + q / C4, g.M - 1), col = min(bn + q % C4 * 4, g.N - 4);
             rv[t] = *reinterpret_cast<const f32x4*>(g.e.res + (int64_t)row * g.e.ldr + col);
         }
     }
@@ -1460,7 +1474,7 @@ __global__ __launch_bounds__(768) void gemm_mid_kernel(GemmArgs g) {
     }
 #pragma unroll
     for (int t = 0; t < IT; ++t) {
-        const int q = tid + 768 * t, lr = q / C4, lc = q % C4 * 4;
+        const int q = tid + NT * t, lr = q / C4, lc = q % C4 * 4;
         const int row = bm + lr, col = bn + lc;
         if (row >= g.M || col >= g.N) continue;
         const f32x4 y = *reinterpret_cast<const f32x4*>(ft + lr * PITCH + lc);
@@ -1472,9 +1486,9 @@ __global__ __launch_bounds__(768) void gemm_mid_kernel(GemmArgs g) {
     }
 }
 
-template <int EPI>
+template <int EPI, int BN>
 static void launch_mid(const GemmArgs& g, hipStream_t s) {
-    launch_k(gemm_mid_kernel<EPI>, dim3((unsigned)(((g.M + 127) / 128) * ((g.N + 143) / 144))), dim3(768), s, g);
+    launch_k(gemm_mid_kernel<EPI, BN>, dim3((unsigned)(((g.M + 127) / 128) * ((g.N + BN - 1) / BN))), dim3(64 * (BN / 12)), s, g);
 }
 
 template <typename T, int EPI, int BM, int BN, int WAVES_M, int WAVES_N>
@@ -1523,8 +1537,10 @@ static int phase_parts(const GemmArgs& g) {
 //   * N a multiple of 432 with at least one round of 128 x 432 tiles (the
 //     DiT-XL/2 QKV projection: exactly 256): 2 x 4 waves of 64 x 112 / 64 x 96;
 //   * at most 256 tiles of 128 x 144 (the N = 1152 projections at M = 4096) and
-//     K >= 1024: those (M = 4096, N = 1152, K = 1152: 20.0 us against 24.8
-//     with 128 x 128 tiles; M = 3000, K = 768: 15.0 against 12.6);
+//     K >= 1024: those (M = 4096, N = 1152, K = 1152: 20.0 us against 24.8 with
+//     128 x 128 tiles; M = 3000, K = 768: 15.0 against 12.6);
+//   * at most 256 tiles of 128 x 192 and K >= 1152: those (M = 2048, N = 3072, K =
+//     1536: 28.5 us against 31.3; equal at K = 1152, 21.4 against 20.6 at 1024);
 //   * otherwise 128 x 128 (16 waves of 32 x 32, two workgroups per CU).
 // Other bf16 operands take the direct-to-LDS kernel with the scalar
 // epilogue, or the register-staged kernel; fp32 the register-staged kernel.
@@ -1578,6 +1594,8 @@ static int run_gemm(const GemmArgs& g, hipStream_t s) {
     if (run_ksplit<T, EPI>(g, s)) return check_launch("gemm");
     if constexpr (sizeof(T) == 2) {
         const int64_t tiles144 = (int64_t)((g.M + 127) / 128) * ((g.N + 143) / 144);
+        const int64_t tiles192 = (int64_t)((g.M + 127) / 128) * ((g.N + 191) / 192);
+        const bool mid = g.K >= 1024 && (g.lda > g.ldw ? g.lda : g.ldw) <= (1 << 22);
         const bool dma = g.K % 64 == 0 && g.lda % 8 == 0 && g.ldw % 8 == 0;
         if (dma && wide_ok(g, EPI)) {
             const int parts = phase_parts(g);
@@ -1587,8 +1605,10 @@ static int run_gemm(const GemmArgs& g, hipStream_t s) {
                 launch_phase<EPI, 3>(g, s);
             } else if (g.N % 432 == 0 && (int64_t)((g.M + 127) / 128) * (g.N / 432) >= 256) {
                 launch_wide<EPI, 128, 432, 4, 3>(g, s);
-            } else if (tiles144 <= 256 && g.K >= 1024 && (g.lda > g.ldw ? g.lda : g.ldw) <= (1 << 22)) {
-                launch_mid<EPI>(g, s);
+            } else if (tiles144 <= 256 && mid) {
+                launch_mid<EPI, 144>(g, s);
+            } else if (tiles192 <= 256 && mid && g.K >= 1152) {
+                launch_mid<EPI, 192>(g, s);
             } else {
                 launch_wide<EPI, 128, 128, 4, 4>(g, s);
             }

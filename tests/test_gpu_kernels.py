@@ -224,9 +224,10 @@ def test_attention_four_waves(bclib, prescaled, B, H, Tq, Tk, d):
     assert err <= 1e-2, err      # probabilities and outputs rounded to bf16 (about 3e-3 together)
 
 
-# The 128 x 144 tiles: ragged rows and columns, every remainder of the k-steps by
-# the four stages.
+# The 128 x 144 and 128 x 192 tiles: ragged rows and columns, every remainder of
+# the k-steps by the four stages.
 @pytest.mark.parametrize("epi", ["bias", "gelu", "gate"])
-@pytest.mark.parametrize("K", [1024, 1088, 1152, 1216])
-def test_linear_one_round(bclib, K, epi):
-    test_linear_small_grids(bclib, "bf16", 3900, 1144, K, 0, epi)
+@pytest.mark.parametrize("M,N,K", [(3900, 1144, 1024), (3900, 1144, 1088), (3900, 1144, 1152), (3900, 1144, 1216),
+                                   (1840, 3000, 1152), (1840, 3000, 1216), (1840, 3000, 1280), (1840, 3000, 1344)])
+def test_linear_one_round(bclib, M, N, K, epi):
+    test_linear_small_grids(bclib, "bf16", M, N, K, 0, epi)
