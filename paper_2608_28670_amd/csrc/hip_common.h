@@ -82,6 +82,32 @@ __device__ __forceinline__ float wave_sum(float v) {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
+// One wave-wide direct-to-LDS load from a wave-uniform base plus a 32-bit byte
+// offset per lane.
+__device__ __forceinline__ void dma16s(const void* base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds) : "memory", "m0");
+}
+
+template <int N> __device__ __forceinline__ void wait_vmcnt() {
+    static_assert(N >= 0 && N < 64, "vmcnt range");
+    // gfx9 s_waitcnt encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] at [15:14]
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+// Wait until at most `later` groups of Q direct-to-LDS loads (issued after the
+// group waited for) are outstanding; `later` >= LMAX waits for all.
+template <int Q, int L = 0, int LMAX = 3> __device__ __forceinline__ void wait_groups(int later) {
+    if constexpr (L >= LMAX) {
+        wait_vmcnt<0>();
+    } else {
+        if (later <= L) {
+            wait_vmcnt<L * Q>();
+            return;
+        }
+        wait_groups<Q, L + 1, LMAX>(later);
+    }
+}
+
 inline int dtype_size(int dt) { return dt == BC_BF16 ? 2 : 4; }
 
 // Check a launch; returns BC_OK or BC_ERR_HIP with the message recorded.

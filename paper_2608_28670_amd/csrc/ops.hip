@@ -178,13 +178,13 @@ int launch_ln_mod(int in_dt, const void* x, int64_t rows, int D, const float* sh
 // (grid.y) and 16 TN output features; the waves deal the k-chunks among
 // themselves (wave w takes chunks w, w + 8, ...) and meet in LDS once at the
 // end, in a fixed order.  What bounds it is the one read of the weights, so
-// they go straight from memory to the MFMA's B operand, 16 bytes a lane, with
-// U chunks of every tile issued before the first is used; splitting k over the
-// waves is what puts enough of them in flight (a workgroup per 256 features
-// with the whole of k behind two barriers left 27 to 72 workgroups: 33 us for
-// the 16 MB of DiT-XL/2's modulation, 79 us for the video model's 113 MB).
-// The activation is applied as the A operand is loaded: each wave needs only
-// its own chunks of it.
+// enough of them have to be in flight: they go straight from memory to the
+// MFMA's B operand, 16 bytes a lane, with U chunks of every tile issued before
+// the first is used.  (A workgroup per 256 features with the whole of k behind
+// two barriers left 27 to 72 workgroups: 33 us for DiT-XL/2's modulation, 79 us for
+// the video model's.)  The activation is applied as the A operand is loaded.
+// This form takes fp32 weights and k that is short or not whole 64-wide steps;
+// the stream below it the rest.
 // ---------------------------------------------------------------------------
 template <typename T> struct SkMma;
 template <> struct SkMma<bf16> {
@@ -300,6 +300,142 @@ __global__ __launch_bounds__(64 * kSkWaves) void skinny_kernel(SkinnyArgs a) {
     }
 }
 
+// The same for bf16 weights with whole 64-wide k-steps, as a stream: a
+// workgroup takes column tile after column tile (16 features each), its waves
+// every eighth k-step of all of them.  The activation of a wave's k-steps is
+// worked out once, into registers; the weights pass through a ring of S stages
+// that only this wave uses, 128 bytes of 16 rows a stage, S stages ahead across
+// tile ends.  (Loaded straight into the MFMA operand, as above, 16 lanes fetch
+// 16 bytes from 16 rows: a fraction of the rate of these loads.)  The partial
+// tiles meet in LDS, one wave finishing each tile while the others go on.
+// 18 432 x 3072 (the video model's modulation, 113 MB): 53 us with the loads
+// straight into operands, 25 now (4.5 TB/s); 9216 x 3072 33 and 21; 6912 x 1152 11.9
+// and 7.4.
+template <int AST, int S>
+__global__ __launch_bounds__(64 * kSkWaves) void skinny_stream_kernel(SkinnyArgs a) {
+    constexpr int STAGE = 16 * 128;
+    __shared__ __attribute__((aligned(1024))) char ring[kSkWaves * S * STAGE];
+    __shared__ __attribute__((aligned(16))) f32x4 red[2][kSkWaves][64];
+    typedef __attribute__((address_space(3))) const char lds_char;
+    typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, grp = lane >> 4, b0 = blockIdx.y * 16;
+    const int tiles = a.N / 16, nk = a.K / 64;
+    const int nt = (tiles - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;    // this workgroup's tiles
+    const int ns = nk > wave ? (nk - wave + kSkWaves - 1) / kSkWaves : 0;             // this wave's k-steps (at most AST)
+    const int items = nt * ns;
+    uint32_t off[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int r = 8 * q + (lane >> 3);
+        off[q] = (uint32_t)r * (uint32_t)(a.K * 2) + ((lane & 7) ^ ((r >> 1) & 7)) * 16;
+    }
+    const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_char*)ring + wave * S * STAGE);
+    // Item i is k-step wave + 8 (i % ns) of tile blockIdx.x + (i / ns) gridDim.x.
+    int it = 0, is = 0;         // tile and step of the next item to load
+    auto issue = [&](int stage) __attribute__((always_inline)) {
+        const char* src = static_cast<const char*>(a.W) +
+                          ((int64_t)(blockIdx.x + (int64_t)it * gridDim.x) * 16 * a.K + (int64_t)(wave + kSkWaves * is) * 64) * 2;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) dma16s(src, off[q], lds + stage * STAGE + q * 1024);
+        if (++is == ns) {
+            is = 0;
+            ++it;
+        }
+    };
+    // The activation: row b0 + r16 of the batch (zero past the last), k = 64 step
+    // + 32 kk + 8 grp ...  Its loads come back first, so that only the weights'
+    // are outstanding while it is worked out.
+    const bool row_ok = b0 + r16 < a.B;
+    const float* in = a.in + (int64_t)min(b0 + r16, a.B - 1) * a.ld_in;
+    const bool vec = reinterpret_cast<uintptr_t>(a.in) % 16 == 0 && a.ld_in % 4 == 0;   // the caller's vectors may be unaligned
+    float v[AST][2][8];
+#pragma unroll
+    for (int j = 0; j < AST; ++j)
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const int k = (wave + kSkWaves * j) * 64 + kk * 32 + grp * 8;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[j][kk][i] = 0.f;
+            if (row_ok && k < a.K) {
+                if (vec) {
+#pragma unroll
+                    for (int i = 0; i < 8; i += 4) {
+                        const f32x4 x = *reinterpret_cast<const f32x4*>(in + k + i);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[j][kk][i + e] = x[e];
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[j][kk][i] = in[k + i];
+                }
+            }
+        }
+    wait_vmcnt<0>();
+#pragma unroll
+    for (int p = 0; p < S; ++p)
+        if (p < items) issue(p);
+    u32x4 af[AST][2];
+#pragma unroll
+    for (int j = 0; j < AST; ++j)
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            if (a.act_in == 1) {
+                // SiLU with one native exp2 and reciprocal (rounded to bf16 next).
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    v[j][kk][i] *= __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * v[j][kk][i]));
+            }
+            af[j][kk] = SkMma<bf16>::pack(v[j][kk]);
+        }
+    lds_char* frag[2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+        frag[kk] = (lds_char*)ring + wave * S * STAGE + r16 * 128 + ((kk * 4 + grp) ^ ((r16 >> 1) & 7)) * 16;
+    int stage = 0, i = 0;
+    for (int t = 0; t < nt; ++t) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < AST; ++j) {
+            if (j < ns) {
+                wait_groups<2, 0, S - 1>(min(S - 1, items - 1 - i));      // item i has landed
+                asm volatile("" ::: "memory");
+                u32x4 w[2];
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk) w[kk] = *(lds_u32x4*)(frag[kk] + stage * STAGE);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // read before the stage is filled again
+                if (i + S < items) issue(stage);
+                stage = stage + 1 == S ? 0 : stage + 1;
+                ++i;
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk) acc = SkMma<bf16>::mma(af[j][kk], w[kk], acc);
+            }
+        }
+        // (Two sets of partial tiles: a wave may be one tile ahead of the one
+        // that finishes, and the barrier of the next tile holds it there.)
+        red[t & 1][wave][lane] = acc;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (wave == t % kSkWaves) {
+            f32x4 sum = red[t & 1][0][lane];
+#pragma unroll
+            for (int w = 1; w < kSkWaves; ++w) sum += red[t & 1][w][lane];
+            const int n = (int)(blockIdx.x + (int64_t)t * gridDim.x) * 16 + r16;
+            const float bv = a.bias ? ld(static_cast<const bf16*>(a.bias) + n) : 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int b = b0 + 4 * grp + r;
+                if (b >= a.B) continue;
+                float v = sum[r] + bv;
+                if (a.act_out == 1) v = silu(v);
+                a.out[(int64_t)b * a.ld_out + n] = v;
+            }
+        }
+    }
+}
+
 template <typename T_>
 static void run_skinny(const SkinnyArgs& a, hipStream_t s) {
     // Features per workgroup: as many tiles (up to four, so that the
@@ -317,8 +453,17 @@ int launch_skinny(int dt, const SkinnyArgs& a, hipStream_t s) {
     if (a.N % 16 || a.K % (dt == BC_BF16 ? 8 : 4)) return fail(BC_ERR_UNSUPPORTED, "skinny linear N=%d K=%d", a.N, a.K);
     if (!a.W || reinterpret_cast<uintptr_t>(a.W) % 16)
         return fail(BC_ERR_INVALID_ARG, "skinny linear weight missing or misaligned");
-    if (dt == BC_BF16) run_skinny<bf16_tag>(a, s);
-    else run_skinny<float>(a, s);
+    if (dt == BC_BF16 && a.K % 64 == 0 && a.K >= 512 && a.K <= 4096) {
+        const int tiles = a.N / 16, per = (tiles + 511) / 512;      // two workgroups a CU, equal shares
+        const dim3 grid((unsigned)((tiles + per - 1) / per), (unsigned)((a.B + 15) / 16)), block(64 * kSkWaves);
+        if (a.K <= 1536) skinny_stream_kernel<3, 4><<<grid, block, 0, s>>>(a);
+        else if (a.K <= 3072) skinny_stream_kernel<6, 4><<<grid, block, 0, s>>>(a);
+        else skinny_stream_kernel<8, 4><<<grid, block, 0, s>>>(a);
+    } else if (dt == BC_BF16) {
+        run_skinny<bf16_tag>(a, s);
+    } else {
+        run_skinny<float>(a, s);
+    }
     return check_launch("skinny linear");
 }
 

@@ -508,7 +508,7 @@ def test_sample_cfg_rejects_unconditional_model(bclib):
 # ragged group of 16; c at any 4-byte alignment.
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
 @pytest.mark.parametrize("B,heads,hd,off", [(1, 2, 32, 0), (16, 16, 72, 0), (17, 2, 72, 1), (3, 7, 64, 0), (33, 30, 64, 3),
-                                            (2, 3, 32, 1), (1, 46, 64, 0)])
+                                            (2, 3, 32, 1), (1, 46, 64, 0), (20, 8, 64, 0), (2, 50, 64, 2)])
 def test_modulation_linear(bclib, dt, B, heads, hd, off):
     if dt == "f32" and hd > 64:
         pytest.skip("fp32 blocks take head dims up to 64")
