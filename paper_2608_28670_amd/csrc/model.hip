@@ -123,9 +123,9 @@ static int qproj(int dt, const void* A, int64_t lda, const void* W, const void* 
 // Rows up to which the QKV projection and the attention of short sequences run
 // as two kernels.  The fused kernel has one workgroup per (sample, head), each
 // with all of the projection's k-steps, so its time does not fall below that of
-// one round: 34 us for one DiT-XL/2 sample (16 workgroups), where the k-split
+// one round: 33 us for one DiT-XL/2 sample (16 workgroups), where the k-split
 // projection and the attention take 9 + 7 us; with four samples (1024 rows) 19 +
-// 7 against 34, with eight about 30 + 9 against 35.
+// 8 against 33, with eight about 30 + 9 against 35.
 constexpr int kFusedQkvRows = 1024;
 
 // One DiT or PixArt block on x [B*T, D] (fp32).  mod: [B, >= 6D] fp32 rows

@@ -546,3 +546,12 @@ def test_modulation_linear(bclib, dt, B, heads, hd, off):
                          ids=["d64_T110_B10", "d32_T256_B5"])
 def test_dit_block_fused_qkv_attention_rows(bclib, hidden, heads, hd, latent, B):
     test_dit_block_fused_qkv_attention(bclib, hidden, heads, hd, latent, B)
+
+
+# The fused kernel's projection at few and at odd counts of its 64-wide k-steps
+# (2, 3, 5 and 9: an odd count starts on the second stage), and one k-step,
+# which takes the projection and the attention as two kernels.
+@pytest.mark.parametrize("hidden,heads,hd", [(128, 4, 32), (192, 3, 64), (320, 10, 32), (576, 8, 72), (64, 1, 64)],
+                         ids=["k2_d32", "k3_d64", "k5_d32", "k9_d72", "k1_d64"])
+def test_dit_block_fused_qkv_attention_steps(bclib, hidden, heads, hd):
+    test_dit_block_fused_qkv_attention(bclib, hidden, heads, hd, (4, 20, 22), 10)
