@@ -1504,7 +1504,7 @@ static int phase_parts(const GemmArgs& g) {
 }
 
 // Tile choice (measured on MI355X over the DiT-XL/2, PixArt and HunyuanVideo
-// block shapes, see the design notes), for bf16 operands with whole 64-wide
+// block shapes), for bf16 operands with whole 64-wide
 // k-steps and an epilogue the wide kernel can vectorise:
 //   * at least one full round of 256 x 288 tiles over the 256 CUs: the phased
 //     kernel;
@@ -1517,7 +1517,7 @@ static int phase_parts(const GemmArgs& g) {
 //     1536: 28.5 us against 31.3; equal at K = 1152, 21.4 against 20.6 at 1024);
 //   * otherwise 128 x 128 (16 waves of 32 x 32, two workgroups per CU).
 // Other bf16 operands take the direct-to-LDS kernel with the scalar
-// epilogue, or the register-staged kernel; fp32 the register-staged kernel.
+// epilogue, or the register-staged kernel, as does fp32 with K % 32 != 0.
 // Before all of these, grids too small for them go to the k-split kernel.
 //
 // bf16: the k-split kernel's tile is the one with the least work per CU, rounds

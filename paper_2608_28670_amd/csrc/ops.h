@@ -42,10 +42,6 @@ int launch_build_cond(int dt, const float* temb, int S, int B, int D, const void
 struct RowList { int row[kMaxSeg]; };
 int launch_gather_silu(int dt, const float* c, int B, int D, const RowList& rows, int n, void* out, hipStream_t s);
 
-// c[b, :] = t[b, :] + table[labels[b], :] (table in `dt`).
-int launch_add_label(int dt, const float* t, const void* table, const int64_t* labels, int B, int D, int n_rows,
-                     float* c, hipStream_t s);
-
 // out[b, seg*N + j] = vec[b, j] + table_seg[j]  (tables in `dt`, N entries each).
 int launch_add_tables(int dt, const float* vec, int64_t ld_vec, const void* const* tables, int nseg, int N, int B,
                       float* out, int64_t ld_out, hipStream_t s);

@@ -540,27 +540,6 @@ int launch_gather_silu(int dt, const float* c, int B, int D, const RowList& rows
     return check_launch("gather_silu");
 }
 
-template <typename T_>
-__global__ void add_label_kernel(const float* t, const elem_t<T_>* table, const int64_t* labels, int B, int D, int n_rows,
-                                 float* c) {
-    typedef elem_t<T_> T;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)B * D) return;
-    const int b = (int)(i / D), n = (int)(i % D);
-    int64_t lab = labels[b];
-    lab = lab < 0 ? 0 : (lab >= n_rows ? n_rows - 1 : lab);   // out-of-range labels are clamped
-    c[i] = t[i] + ld(table + lab * D + n);
-}
-
-int launch_add_label(int dt, const float* t, const void* table, const int64_t* labels, int B, int D, int n_rows,
-                     float* c, hipStream_t s) {
-    const int64_t n = (int64_t)B * D;
-    const unsigned g = (unsigned)((n + 255) / 256);
-    if (dt == BC_BF16) add_label_kernel<bf16_tag><<<g, 256, 0, s>>>(t, static_cast<const bf16*>(table), labels, B, D, n_rows, c);
-    else add_label_kernel<float><<<g, 256, 0, s>>>(t, static_cast<const float*>(table), labels, B, D, n_rows, c);
-    return check_launch("add_label");
-}
-
 struct TableArgs { const void* tab[kMaxSeg]; };
 
 template <typename T_>
