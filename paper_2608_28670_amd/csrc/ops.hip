@@ -151,9 +151,13 @@ static int run_ln_rows(const void* x, int64_t rows, int D, const float* shift, c
 // reduced), four for rows of up to 1280 values when there are at least 8192
 // of them (PixArt's 16 384 rows of 1152: 20.6 -> 18.6 us; DiT-XL/2's 4096
 // rows are fastest with two: 7.7 us against 8.6 with four and 8.0 with one).
+// One for up to 2048 rows, where two leave a CU fewer than four waves and the
+// second row only lengthens the chain: 1020 rows of 1152 4.3 us against 5.1,
+// 1846 of 3072 10.9 against 11.8, 128 of 128 3.0 against 3.5.
 template <typename Tin, typename Tout>
 static int run_ln(const void* x, int64_t rows, int D, const float* shift, const float* scale, int64_t ld_mod, int rps,
                   void* h, hipStream_t s) {
+    if (rows <= 2048) return run_ln_rows<Tin, Tout, 1>(x, rows, D, shift, scale, ld_mod, rps, h, s);
     if (D <= 1280 && rows >= 8192) return run_ln_rows<Tin, Tout, 4>(x, rows, D, shift, scale, ld_mod, rps, h, s);
     return run_ln_rows<Tin, Tout, 2>(x, rows, D, shift, scale, ld_mod, rps, h, s);
 }

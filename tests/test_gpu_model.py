@@ -555,3 +555,9 @@ def test_dit_block_fused_qkv_attention_rows(bclib, hidden, heads, hd, latent, B)
                          ids=["k2_d32", "k3_d64", "k5_d32", "k9_d72", "k1_d64"])
 def test_dit_block_fused_qkv_attention_steps(bclib, hidden, heads, hd):
     test_dit_block_fused_qkv_attention(bclib, hidden, heads, hd, (4, 20, 22), 10)
+
+
+# The LayerNorm's rows per wave: one up to 2048 rows, two above.
+@pytest.mark.parametrize("latent,B", [((4, 32, 32), 8), ((4, 10, 82), 10)], ids=["rows2048", "rows2050"])
+def test_dit_block_layernorm_rows(bclib, latent, B):
+    test_dit_block_fused_qkv_attention(bclib, 256, 8, 32, latent, B)
