@@ -1084,6 +1084,8 @@ int launch_attention(int dtype, AttnArgs a, hipStream_t s) {
                          c16 = cost(64, a.d <= 72 ? 733 : 550);
             if (c64 <= c32 && c64 <= c16)
                 rc = a.q_scaled ? run_attention_dma<4, 8, 2, true, true>(a, a.d, s) : run_attention_dma<4, 8, 2>(a, a.d, s);
+            else if (c32 <= c16 && wgs(128) <= 256)
+                rc = a.q_scaled ? run_attention_dma<1, 8, 2, true, true>(a, a.d, s) : run_attention_dma<1, 8, 2>(a, a.d, s);
             else if (c32 <= c16)
                 rc = a.q_scaled ? run_attention_dma<2, 4, 2, true, true>(a, a.d, s) : run_attention_dma<2, 4, 2>(a, a.d, s);
             else
