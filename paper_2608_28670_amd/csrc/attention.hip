@@ -1069,6 +1069,10 @@ int launch_attention(int dtype, AttnArgs a, hipStream_t s) {
     // in 65, 8 x 32 in 99; 1 x 16 x 1020^2 x 72: 4 x 16 in 16.4 us, 4 x 32 in
     // 20.1; at d = 128 two 4-wave workgroups a CU, whose barriers do not line
     // up, ran 24 x 14 566 tokens 6 % faster than one of 8 waves.
+    // Where the 128-query workgroups make at most one round, 8 waves of 16
+    // queries instead of 4 of 32, which would leave one wave on each SIMD (3 x 15
+    // heads of 337^2 x 64: 8.9 us against 10.4; 18 of 1126 x 558 x 72: 13.6
+    // against 15.1; 2 x 19 of 432^2 x 128: 15.7 against 17.3).
     int rc;
     if (dtype == BC_BF16) {
         const int Tk = a.Tk0 + a.Tk1, Tq = a.Tq0 + a.Tq1;
