@@ -301,11 +301,6 @@ __global__ __launch_bounds__(kAttnThreads) void attention_kernel(AttnArgs a) {
 // 128 or 256 bytes are XOR-swizzled by 16-byte chunk so the 16-row fragment
 // reads hit distinct banks (a 144-byte row of d = 72 already does).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void dma16a(const void* src, const void* lds_base) {
-    const unsigned m0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lds_base);
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(m0) : "memory", "m0");
-}
-
 template <int HD> struct KvLayout {
     static constexpr int CPR = HD / 8;                       // 16-byte chunks per row
     static constexpr int RPB = (HD * 2) >= 256 ? 1 : 256 / (HD * 2);   // rows per 256 bytes
@@ -683,8 +678,8 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
             const int ic = icol(q);
             const bf16* kr = seg_row<bf16>(a.k0, a.k1, a.Tk0, a.Tk1, a.ldk, b, key) + ic;
             const bf16* vr = seg_row<bf16>(a.v0, a.v1, a.Tk0, a.Tk1, a.ldv, b, key) + ic;
-            dma16a(kr, &sK[buf][64 * j * 8]);
-            dma16a(vr, &sV[buf][64 * j * 8]);
+            dma16(kr, &sK[buf][64 * j * 8]);
+            dma16(vr, &sV[buf][64 * j * 8]);
         }
     };
     auto issue = [&](int k0, int buf) {
@@ -705,8 +700,8 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
             for (int q = 0; q < NJ; ++q) {
                 const int j = wave + NWV * q;
                 if (j >= LY::CPR) break;
-                dma16a(kb + koff[q], &sK[buf][64 * j * 8]);
-                dma16a(vb + (VFROMK ? koff[q] + irow(q) * (int)(a.ldv - a.ldk) : voff[VFROMK ? 0 : q]), &sV[buf][64 * j * 8]);
+                dma16(kb + koff[q], &sK[buf][64 * j * 8]);
+                dma16(vb + (VFROMK ? koff[q] + irow(q) * (int)(a.ldv - a.ldk) : voff[VFROMK ? 0 : q]), &sV[buf][64 * j * 8]);
             }
         } else {
             issue_rows(k0, buf);

@@ -227,15 +227,6 @@ template <int SW> __device__ __forceinline__ int swz_of(int row) {
 }
 __device__ __forceinline__ int swz(int row) { return swz_of<0>(row); }
 
-// One wave-wide direct-to-LDS load: each lane's 16 bytes at `src` land at
-// lds_base + 16 * lane.  Issued as inline assembly so that the only waits on
-// it are the explicit vmcnt waits of the pipeline (the compiler would
-// otherwise drain every outstanding load before each LDS read and barrier).
-__device__ __forceinline__ void dma16(const void* src, const void* lds_base) {
-    const unsigned m0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lds_base);   // wave-uniform
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(m0) : "memory", "m0");
-}
-
 template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, bool SEG, int SW = 0>
 __device__ __forceinline__ void gemm_dma_body(GemmArgs g, const GemmSeg* sg) {
     typedef bf16 T;

@@ -82,10 +82,20 @@ __device__ __forceinline__ float wave_sum(float v) {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
-// One wave-wide direct-to-LDS load from a wave-uniform base plus a 32-bit byte
-// offset per lane.
+// One wave-wide direct-to-LDS load: each lane's 16 bytes at `src` land at
+// lds_base + 16 * lane.  Issued as inline assembly so that the only waits on
+// it are the explicit vmcnt waits of the pipeline (the compiler would
+// otherwise drain every outstanding load before each LDS read and barrier).
+// The load reads its LDS address from M0 and needs one wait state after the
+// write of M0 (s_nop 0); the compiler adds none inside an asm block.
+__device__ __forceinline__ void dma16(const void* src, const void* lds_base) {
+    const unsigned m0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lds_base);   // wave-uniform
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(m0) : "memory", "m0");
+}
+
+// The same from a wave-uniform base plus a 32-bit byte offset per lane.
 __device__ __forceinline__ void dma16s(const void* base, uint32_t off, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds) : "memory", "m0");
 }
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
