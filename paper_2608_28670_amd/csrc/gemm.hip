@@ -1202,7 +1202,7 @@ __global__ __launch_bounds__(64 * WK) void gemm_ksplit_kernel(GemmArgs g, int ve
         if (p < n) issue(p, p);
     int stage = 0;
     for (int i = 0; i < n; ++i) {
-        wait_groups<Q, 0, S - 1>(min(S - 1, n - 1 - i));       // step i has landed; later ones may be on their way
+        wait_groups<Q, S - 1>(n - 1 - i);       // step i has landed; later ones may be on their way
         asm volatile("" ::: "memory");
         u32x4 fa[2][TM], fw[2][TN];
 #pragma unroll
@@ -1325,8 +1325,8 @@ __global__ __launch_bounds__(64 * (BN / 12)) void gemm_mid_kernel(GemmArgs g) {
             if (q + 1 < Q || more) dma16s(base[q] + (int64_t)k * 128, off[q], ldsw + st * STAGE + q * NW * 1024);
     };
     auto wait_steps = [&](int later) __attribute__((always_inline)) {      // at most `later` (0 to 2) steps' loads outstanding
-        if (more) wait_groups<Q, 0, 3>(later);
-        else wait_groups<Q - 1, 0, 3>(later);
+        if (more) wait_groups<Q, 2>(later);
+        else wait_groups<Q - 1, 2>(later);
     };
     const uint32_t c = (uint32_t)((kg * 4 + grp) ^ ((frow >> 1) & 7)) * 16;
     lds_char* pA = (lds_char*)sm + (wm * 64 + frow) * 128 + c;

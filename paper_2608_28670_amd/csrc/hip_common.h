@@ -104,17 +104,18 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
-// Wait until at most `later` groups of Q direct-to-LDS loads (issued after the
-// group waited for) are outstanding; `later` >= LMAX waits for all.
-template <int Q, int L = 0, int LMAX = 3> __device__ __forceinline__ void wait_groups(int later) {
-    if constexpr (L >= LMAX) {
+// Wait until at most min(later, LMAX) groups of Q direct-to-LDS loads, issued
+// after the group waited for, are outstanding.  A ring of S stages has S - 1
+// later groups in its steady state: LMAX = S - 1, tested first.
+template <int Q, int LMAX> __device__ __forceinline__ void wait_groups(int later) {
+    if constexpr (LMAX == 0) {
         wait_vmcnt<0>();
     } else {
-        if (later <= L) {
-            wait_vmcnt<L * Q>();
+        if (later >= LMAX) {
+            wait_vmcnt<LMAX * Q>();
             return;
         }
-        wait_groups<Q, L + 1, LMAX>(later);
+        wait_groups<Q, LMAX - 1>(later);
     }
 }
 

@@ -313,8 +313,10 @@ __global__ __launch_bounds__(64 * kSkWaves) void skinny_kernel(SkinnyArgs a) {
 // 16 bytes from 16 rows: a fraction of the rate of these loads.)  The partial
 // tiles meet in LDS, one wave finishing each tile while the others go on.
 // 18 432 x 3072 (the video model's modulation, 113 MB): 53 us with the loads
-// straight into operands, 25 now (4.5 TB/s); 9216 x 3072 33 and 21; 6912 x 1152 11.9
-// and 7.4.
+// straight into operands, 21 now (5.4 TB/s); 6912 x 1152 11.9 and 7.1.  One
+// sample of 24 576 x 4096: 46.7 us with a ring that every step drained, 35.8 now
+// (17 to 32 samples 92 and 75); up to k = 3072, where a CU holds two workgroups,
+// the two rings cover each other and it made no difference.
 template <int AST, int S>
 __global__ __launch_bounds__(64 * kSkWaves) void skinny_stream_kernel(SkinnyArgs a) {
     constexpr int STAGE = 16 * 128;
@@ -403,7 +405,7 @@ __global__ __launch_bounds__(64 * kSkWaves) void skinny_stream_kernel(SkinnyArgs
 #pragma unroll
         for (int j = 0; j < AST; ++j) {
             if (j < ns) {
-                wait_groups<2, 0, S - 1>(min(S - 1, items - 1 - i));      // item i has landed
+                wait_groups<2, S - 1>(items - 1 - i);      // item i has landed
                 asm volatile("" ::: "memory");
                 u32x4 w[2];
 #pragma unroll

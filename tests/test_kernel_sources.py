@@ -1,7 +1,12 @@
-"""Properties of the kernels' sources that a run cannot show reliably (CPU)."""
+"""Properties of the kernels' sources, and of the gfx950 assembly they compile
+to, that a run cannot show reliably (CPU)."""
 import glob
 import os
 import re
+
+import pytest
+
+from paper_2608_28670_amd import build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2608_28670_amd", "csrc")
@@ -23,3 +28,60 @@ def test_lds_loads_wait_after_m0():
                     found += 1
                     assert i > 0 and ops[i - 1].startswith("s_nop"), f"{os.path.basename(path)}: {code}"
     assert found >= 2      # the loads with per-lane addresses and with a uniform base
+
+
+class Kernel:
+    """One kernel of a listing: its instructions (labels included) and resources."""
+
+    def __init__(self):
+        self.code, self.vgprs, self.spills, self.lds = [], None, None, None
+
+
+def _listing(source, tmp):
+    """{mangled name: Kernel} of one HIP source, compiled as the library is."""
+    out = os.path.join(str(tmp), source + ".s")
+    build._run([build._hipcc(), *build.HIP_FLAGS, "-I", CSRC, "-I", build.INCLUDE, "--cuda-device-only", "-S",
+                os.path.join(CSRC, source), "-o", out])
+    with open(out) as f:
+        text = f.read()
+    kernels, cur = {}, None
+    for line in text.splitlines():
+        m = re.match(r"(_Z\w+):", line)
+        if m:
+            cur = kernels.setdefault(m.group(1), Kernel())
+        t = line.split(";")[0].strip()
+        if cur is not None and t and not (t.startswith(".") and not t.endswith(":")):
+            cur.code.append(t)
+            if t == "s_endpgm":
+                cur = None
+    for m in re.finditer(r"\.group_segment_fixed_size: (\d+)(?:(?!\.group_segment).)*?\.name:\s+(\S+)(?:(?!\.group_segment).)*?"
+                         r"\.vgpr_count:\s+(\d+)\s+\.vgpr_spill_count: (\d+)", text, re.S):
+        k = kernels[m.group(2)]
+        k.lds, k.vgprs, k.spills = int(m.group(1)), int(m.group(3)), int(m.group(4))
+    return kernels
+
+
+@pytest.fixture(scope="module")
+def ops_listing(tmp_path_factory):
+    return _listing("ops.hip", tmp_path_factory.mktemp("ops"))
+
+
+def _template_args(name, kernel):
+    """The integer template arguments of an instantiation, or None for another kernel."""
+    if kernel + "I" not in name:
+        return None
+    return [int(v) for v in re.findall(r"L[ib](\d+)E", name.split(kernel, 1)[1].split("EEv")[0] + "E")]
+
+
+def test_weight_stream_keeps_its_ring_filled(ops_listing):
+    """The conditioning linear's weight stream has S stages of two loads; its
+    steady state waits for the oldest only: S - 1 stages stay on their way."""
+    found = 0
+    for name, k in ops_listing.items():
+        t = _template_args(name, "skinny_stream_kernel")
+        if not t:
+            continue
+        found += 1
+        waits = {int(m.group(1)) for c in k.code for m in [re.match(r"s_waitcnt.*vmcnt\((\d+)\)", c)] if m}
+        assert 2 * (t[1] - 1) in waits, (name, sorted(waits))
+    assert found == 3
