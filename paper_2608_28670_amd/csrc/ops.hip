@@ -317,8 +317,13 @@ __global__ __launch_bounds__(64 * kSkWaves) void skinny_kernel(SkinnyArgs a) {
 // sample of 24 576 x 4096: 46.7 us with a ring that every step drained, 35.8 now
 // (17 to 32 samples 92 and 75); up to k = 3072, where a CU holds two workgroups,
 // the two rings cover each other and it made no difference.
-template <int AST, int S>
-__global__ __launch_bounds__(64 * kSkWaves) void skinny_stream_kernel(SkinnyArgs a) {
+// WGS: workgroups that a CU holds at once, which the launcher's grid counts on.
+// Two where the activation (16 AST values a lane) leaves them 128 registers a
+// wave; one at AST = 8, which takes 142 (with a grid of two there, 1 x 24 576 x
+// 4096 took 35.8 us against 34.9, and with 20 samples 75 against 68).
+template <int AST, int S, int WGS>
+__global__ __launch_bounds__(64 * kSkWaves) __attribute__((amdgpu_waves_per_eu(2 * WGS))) void skinny_stream_kernel(
+    SkinnyArgs a) {
     constexpr int STAGE = 16 * 128;
     __shared__ __attribute__((aligned(1024))) char ring[kSkWaves * S * STAGE];
     __shared__ __attribute__((aligned(16))) f32x4 red[2][kSkWaves][64];
@@ -453,6 +458,14 @@ static void run_skinny(const SkinnyArgs& a, hipStream_t s) {
     else skinny_kernel<T_, 1><<<dim3(tiles, rows), block, 0, s>>>(a);
 }
 
+// One round of workgroups with equal shares of the column tiles.
+template <int AST, int S, int WGS>
+static void run_skinny_stream(const SkinnyArgs& a, hipStream_t s) {
+    const int tiles = a.N / 16, per = (tiles + 256 * WGS - 1) / (256 * WGS);
+    const dim3 grid((unsigned)((tiles + per - 1) / per), (unsigned)((a.B + 15) / 16)), block(64 * kSkWaves);
+    skinny_stream_kernel<AST, S, WGS><<<grid, block, 0, s>>>(a);
+}
+
 int launch_skinny(int dt, const SkinnyArgs& a, hipStream_t s) {
     if (a.B <= 0) return BC_OK;
     if (a.B > 64) return fail(BC_ERR_UNSUPPORTED, "conditioning batch %d > 64", a.B);
@@ -460,11 +473,9 @@ int launch_skinny(int dt, const SkinnyArgs& a, hipStream_t s) {
     if (!a.W || reinterpret_cast<uintptr_t>(a.W) % 16)
         return fail(BC_ERR_INVALID_ARG, "skinny linear weight missing or misaligned");
     if (dt == BC_BF16 && a.K % 64 == 0 && a.K >= 512 && a.K <= 4096) {
-        const int tiles = a.N / 16, per = (tiles + 511) / 512;      // two workgroups a CU, equal shares
-        const dim3 grid((unsigned)((tiles + per - 1) / per), (unsigned)((a.B + 15) / 16)), block(64 * kSkWaves);
-        if (a.K <= 1536) skinny_stream_kernel<3, 4><<<grid, block, 0, s>>>(a);
-        else if (a.K <= 3072) skinny_stream_kernel<6, 4><<<grid, block, 0, s>>>(a);
-        else skinny_stream_kernel<8, 4><<<grid, block, 0, s>>>(a);
+        if (a.K <= 1536) run_skinny_stream<3, 4, 2>(a, s);
+        else if (a.K <= 3072) run_skinny_stream<6, 4, 2>(a, s);
+        else run_skinny_stream<8, 4, 1>(a, s);
     } else if (dt == BC_BF16) {
         run_skinny<bf16_tag>(a, s);
     } else {

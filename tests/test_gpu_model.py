@@ -539,6 +539,13 @@ def test_modulation_linear(bclib, dt, B, heads, hd, off):
     assert err <= (3e-3 if dt == "bf16" else 2e-6), err
 
 
+# The widest weight stream (k = 4096: all eight k-steps of every wave), whose
+# workgroups a CU holds one at a time.
+@pytest.mark.parametrize("B", [1, 17])
+def test_modulation_linear_widest(bclib, B):
+    test_modulation_linear(bclib, "bf16", B, 64, 64, 0)
+
+
 # The fused QKV projection + attention at more than 1024 rows (fewer take the
 # projection and the attention as two kernels): a ragged last key tile and a
 # full one, head dims 64 and 32.

@@ -85,3 +85,19 @@ def test_weight_stream_keeps_its_ring_filled(ops_listing):
         waits = {int(m.group(1)) for c in k.code for m in [re.match(r"s_waitcnt.*vmcnt\((\d+)\)", c)] if m}
         assert 2 * (t[1] - 1) in waits, (name, sorted(waits))
     assert found == 3
+
+
+def test_weight_stream_workgroups_are_resident(ops_listing):
+    """The weight stream's grid is one round of the workgroups that the
+    launcher takes a CU to hold (the third template argument): registers (512
+    a SIMD, in eights) and LDS (160 KB) must allow them."""
+    found = 0
+    for name, k in ops_listing.items():
+        t = _template_args(name, "skinny_stream_kernel")
+        if not t:
+            continue
+        found += 1
+        assert len(t) == 3 and k.spills == 0, (name, k.spills)
+        waves_per_simd = 512 // (-(-k.vgprs // 8) * 8)
+        assert min(4 * waves_per_simd // 8, 160 * 1024 // k.lds) == t[2], (name, k.vgprs, k.lds)
+    assert found == 3
