@@ -611,6 +611,13 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
     TileArr* sV = reinterpret_cast<TileArr*>(QKV ? sX_ + NB * TILE : sV_);
     bf16* sQ = sX_ + 2 * NB * TILE;     // QKV only
 
+    // The small resident grids are one chain of latencies: all the arguments in
+    // one round of scalar loads (3 x 65 x 256 at d = 128: 8.4 us without, 8.2 with).
+    if constexpr (!STREAM && !QKV && NWV == 4) {
+        const unsigned nblk = gridDim.x;
+        asm volatile("" : : "s"(nblk), "s"(a.Tq0), "s"(a.Tk0), "s"(a.k0), "s"(a.k1), "s"(a.v0), "s"(a.v1), "s"(a.ldk),
+                     "s"(a.ldv), "s"(a.q0), "s"(a.ldq), "s"(a.H), "s"(a.o0), "s"(a.ldo), "s"(a.scale_log2));
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int Tq = a.Tq0 + a.Tq1, Tk = a.Tk0 + a.Tk1;
@@ -734,7 +741,6 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
 
     f32x4 o[QG][S::DV / 16], osum[QG];
     float m_run[QG];
-    const bool o8 = (a.ldo & 3) == 0 && ((reinterpret_cast<uintptr_t>(a.o0) | reinterpret_cast<uintptr_t>(a.o1)) & 7) == 0;
 #pragma unroll
     for (int g = 0; g < QG; ++g) {
         m_run[g] = STREAM ? 0.f : -INFINITY;     // the streaming tile's reference is set by its first tile
@@ -795,7 +801,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
     // queries).  Keys past Tk occur in the last tile only; their score
     // accumulators start at -inf, one select per score slot shared by the query
     // groups, which keeps the tile one basic block for the scheduler.
-    auto tile = [&](int k0, const bf16* K, const bf16* V) __attribute__((always_inline)) {
+    auto tile = [&](int k0, lds_char* Kb, lds_char* Vb, float c) __attribute__((always_inline)) {
         f32x4 init[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -807,12 +813,12 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
         for (int j = 0; j < 4; ++j) {
 #pragma unroll
             for (int g = 0; g < QG; ++g) s[g][j] = init[j];
-            const int krow = 16 * j + ql;
 #pragma unroll
-            for (int c = 0; c < S::n32x; ++c) {
-                const bf16x8 kf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(K + LY::at(krow, 32 * c + grp * 8)));
+            for (int i = 0; i < S::n32x; ++i) {
+                const bf16x8 kf = __builtin_bit_cast(
+                    bf16x8, *(__attribute__((address_space(3))) const u32x4*)(Kb + kofs[i] + 16u * j * ROWB));
 #pragma unroll
-                for (int g = 0; g < QG; ++g) s[g][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[g][c], s[g][j], 0, 0, 0);
+                for (int g = 0; g < QG; ++g) s[g][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[g][i], s[g][j], 0, 0, 0);
             }
         }
         // Softmax in the log2 domain on raw scores (the scale is positive, so
@@ -820,7 +826,6 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
         // The reference max m_run moves only when some lane's row max exceeds
         // it by more than 8 (log2 units), so the rescale of O and l is rare
         // after the first tiles; until then p = 2^(s c - m c) stays below 2^8.
-        const float c = a.scale_log2;
 #pragma unroll
         for (int g = 0; g < QG; ++g) {
             float mloc = -INFINITY;
@@ -846,7 +851,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
                 }
         }
 
-        pv((lds_char*)V, s);
+        pv(Vb, s);
     };
 
     // Streaming tile.  The reference max m of a query moves (with O and the row
@@ -940,9 +945,32 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
     };
 
     if constexpr (!STREAM) {
+        // What needs no K or V (accumulators, operand addresses, the scale) is
+        // worked out while they are on their way; the compiler puts it behind the
+        // wait, where every wave of the workgroup does it at once: 2 x 19 x 2624 x
+        // 207 at d = 64 19.1 us so and 18.8 now, 18 x 1178 x 137 at d = 128 9.26 and
+        // 9.10.  d = 72 keeps its order: addresses held over the wait are ten
+        // registers, and with two query groups the key loop came out slower.
+        float c = a.scale_log2;
+        if constexpr (!QKV && !(HD == 72 && QG == 2)) {
+#pragma unroll
+            for (int g = 0; g < QG; ++g) {
+                asm volatile("" : "+v"(m_run[g]));
+                if constexpr (!PADSUM) asm volatile("" : "+v"(osum[g]));
+#pragma unroll
+                for (int i = 0; i < S::DV / 16; ++i) asm volatile("" : "+v"(o[g][i]));
+            }
+        }
+        if constexpr (!QKV && HD != 72) {
+            asm volatile("" : "+s"(c));
+#pragma unroll
+            for (int i = 0; i < S::n32x; ++i) asm volatile("" : "+v"(kofs[i]));
+#pragma unroll
+            for (int i = 0; i < S::DV / 16; ++i) asm volatile("" : "+v"(vofs[i]));
+        }
         __builtin_amdgcn_s_waitcnt((0 & 15) | (7 << 4) | (15 << 8));   // vmcnt(0): this wave's loads
         __syncthreads();
-        for (int t = 0; t < ntiles; ++t) tile(t * kKTile, sK[t], sV[t]);
+        for (int t = 0; t < ntiles; ++t) tile(t * kKTile, (lds_char*)sK[t], (lds_char*)sV[t], c);
     } else {
         // Unrolled by two so that each step's buffer is a compile-time constant.
         auto step = [&](int t, auto bufc) __attribute__((always_inline)) {
@@ -974,20 +1002,16 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
         if (myq[g] < Tq) {
             bf16* orow = const_cast<bf16*>(seg_row<bf16>(a.o0, a.o1, a.Tq0, a.Tq1, a.ldo, b, myq[g])) + col0;
             // A lane holds four consecutive d of each 16-row block: one 8-byte
-            // store each where the output rows are 8-byte aligned.
+            // store each, at any alignment of the output (a separate path for
+            // unaligned rows compiled to the same stores behind branches).
 #pragma unroll
             for (int i = 0; i < S::DV / 16; ++i) {
                 const int d = 16 * i + 4 * grp;     // HD % 4 == 0: all four in or all out
                 if (d >= HD) continue;
-                if (o8) {
-                    bf16x4 w;
+                bf16x4 w;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) w[r] = (bf16)(o[g][i][r] * inv);
-                    *reinterpret_cast<bf16x4*>(orow + d) = w;
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) st(orow + d + r, o[g][i][r] * inv);
-                }
+                for (int r = 0; r < 4; ++r) w[r] = (bf16)(o[g][i][r] * inv);
+                __builtin_memcpy(orow + d, &w, sizeof w);
             }
         }
     }

@@ -135,6 +135,23 @@ def test_attention_unaligned_output(bclib, B, H, Tq, Tk, d):
     assert float(buf[:2].abs().sum()) == 0.0     # nothing written before the output
 
 
+# Output rows at every 2-byte alignment, from the resident and the streaming loops.
+@pytest.mark.parametrize("off", [1, 2, 3, 4])
+@pytest.mark.parametrize("B,H,Tq,Tk,d", [(1, 2, 70, 100, 72), (1, 2, 70, 300, 128)])
+def test_attention_output_alignment(bclib, B, H, Tq, Tk, d, off):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(off)
+    q, k, v = (torch.empty((B, T, H, d), device=DEV).normal_(generator=g).bfloat16() for T in (Tq, Tk, Tk))
+    want = torch.empty_like(q)
+    bclib.attention(q, k, v, want)
+    buf = torch.full((q.numel() + 8,), 7.0, dtype=torch.bfloat16, device=DEV)
+    out = buf[off:off + q.numel()].view(q.shape)
+    bclib.attention(q, k, v, out)
+    torch.cuda.synchronize()
+    assert bool((out == want).all())
+    assert bool((buf[:off] == 7.0).all()) and bool((buf[off + q.numel():] == 7.0).all())    # nothing written outside
+
+
 def test_attention_prescaled_rejects_fp32(bclib):
     z = torch.zeros((1, 4, 1, 32), dtype=torch.float32, device=DEV)
     with pytest.raises(bclib.BCError) as e:

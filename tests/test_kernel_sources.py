@@ -49,11 +49,11 @@ def _listing(source, tmp):
         m = re.match(r"(_Z\w+):", line)
         if m:
             cur = kernels.setdefault(m.group(1), Kernel())
+        if line.startswith(".Lfunc_end"):
+            cur = None
         t = line.split(";")[0].strip()
         if cur is not None and t and not (t.startswith(".") and not t.endswith(":")):
             cur.code.append(t)
-            if t == "s_endpgm":
-                cur = None
     for m in re.finditer(r"\.group_segment_fixed_size: (\d+)(?:(?!\.group_segment).)*?\.name:\s+(\S+)(?:(?!\.group_segment).)*?"
                          r"\.vgpr_count:\s+(\d+)\s+\.vgpr_spill_count: (\d+)", text, re.S):
         k = kernels[m.group(2)]
@@ -64,6 +64,11 @@ def _listing(source, tmp):
 @pytest.fixture(scope="module")
 def ops_listing(tmp_path_factory):
     return _listing("ops.hip", tmp_path_factory.mktemp("ops"))
+
+
+@pytest.fixture(scope="module")
+def attention_listing(tmp_path_factory):
+    return _listing("attention.hip", tmp_path_factory.mktemp("attention"))
 
 
 def _template_args(name, kernel):
@@ -101,3 +106,37 @@ def test_weight_stream_workgroups_are_resident(ops_listing):
         waves_per_simd = 512 // (-(-k.vgprs // 8) * 8)
         assert min(4 * waves_per_simd // 8, 160 * 1024 // k.lds) == t[2], (name, k.vgprs, k.lds)
     assert found == 3
+
+
+def test_resident_attention_sets_up_before_its_wait(attention_listing):
+    """Between the wait for the resident key tiles and the key loop lies no
+    load of an argument, and (d = 72 apart) none of the set-up that needs no
+    keys: accumulators, operand addresses."""
+    found = 0
+    for name, k in attention_listing.items():
+        t = _template_args(name, "attention_dma_kernel")      # d, QG, waves, buffers, STREAM, QS, QKV
+        if not t or t[4] or t[6] or t[0] == 72:
+            continue
+        found += 1
+        at = max(i for i, c in enumerate(k.code) if c == "s_barrier")
+        setup = []
+        for c in k.code[at + 1:]:
+            if c.endswith(":"):
+                break
+            setup.append(c)
+        assert not any(c.startswith("s_load") for c in setup), (name, setup)
+        assert len(setup) <= 16, (name, len(setup))
+    assert found == 9
+
+
+def test_attention_stores_its_rows_without_branches(attention_listing):
+    """One 8-byte store per query group and 16-row block of the output, with no second form of it."""
+    found = 0
+    for name, k in attention_listing.items():
+        t = _template_args(name, "attention_dma_kernel")
+        if not t:
+            continue
+        found += 1
+        stores = [c.split()[0] for c in k.code if c.startswith("global_store")]
+        assert stores == ["global_store_dwordx2"] * (t[1] * -(-t[0] // 16)), (name, stores)
+    assert found >= 30
