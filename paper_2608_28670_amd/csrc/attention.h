@@ -38,6 +38,16 @@ struct AttnArgs {
 // Softmax scale in log2 units: log2(e) / sqrt(head_dim).
 inline float attn_q_scale(int head_dim) { return 1.4426950408889634f / sqrtf((float)head_dim); }
 
+// A workgroup of the bf16 attention: `waves` waves of `qg` groups of 16
+// queries; `stream`: the key tiles pass through a double buffer, else they are
+// all resident in LDS.  bc_attention_variant reports the choice for a call, so
+// that the tests can tell which kernel each of their shapes runs.
+struct AttnVariant {
+    int qg, waves;
+    bool stream;
+};
+extern "C" int bc_attention_variant(int B, int H, int Tq, int Tk, int d, int* qg, int* waves, int* stream);
+
 bool attention_supported(int head_dim);
 int launch_attention(int dtype, AttnArgs a, hipStream_t s);
 

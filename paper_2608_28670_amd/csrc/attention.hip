@@ -1057,6 +1057,42 @@ static int run_attention(const AttnArgs& a, int hd, hipStream_t s) {
 
 bool attention_supported(int hd) { return hd == 32 || hd == 64 || hd == 72 || hd == 128; }
 
+// The workgroup's shape for a call.  Up to 256 keys, every key tile is resident
+// in LDS (one load, no barriers in the key loop): 8 waves of 32 queries when
+// that still leaves two rounds of 256-query workgroups (PixArt's
+// cross-attention to 120 keys at batch 4: 35.1 -> 28.7 us in a probe, 59.6 ->
+// 58.5 ms of attention per sampling run), 4 waves of 16 when those make at most
+// one round (one DiT-XL/2 sample: 6.5 us against 7.4 with 8 waves), else 8
+// waves of 16 (DiT-XL/2's self-attention at batch 16: 13.9 us against 17.6 with
+// 4 waves).
+// Longer sequences, waves over a double buffer: 8 waves of 64 queries (d <= 72:
+// every K/V fragment read from LDS feeds four MFMAs; at d = 128 they would
+// spill), 4 waves of 32, or 4 of 16; the one whose fullest CU (rounds of 256
+// workgroups times queries each) finishes first at the rate that it reaches on
+// a full grid (4 x 16 x 4096^2 x 72: 1014, 965 and 733 TFLOP/s; 550 for 4 x 16
+// at d = 128, where two workgroups fill a CU's LDS: 24 heads of 1846^2 71 us
+// against 56 with 4 x 32).  2 x 16 x 2050^2 x 64, unscaled: 4 x 32 queries in 63
+// us, 4 x 16 in 65, 8 x 32 in 99; 1 x 16 x 1020^2 x 72: 4 x 16 in 16.4 us, 4 x 32
+// in 20.1; at d = 128 two 4-wave workgroups a CU, whose barriers do not line up,
+// ran 24 x 14 566 tokens 6 % faster than one of 8 waves.
+// Where the 128-query workgroups make at most one round, 8 waves of 16 queries
+// instead of 4 of 32, which would leave one wave on each SIMD (3 x 15 heads of
+// 337^2 x 64: 8.9 us against 10.4; 18 of 1126 x 558 x 72: 13.6 against 15.1; 2 x
+// 19 of 432^2 x 128: 15.7 against 17.3).
+static AttnVariant attention_variant(int B, int H, int Tq, int Tk, int d) {
+    const int64_t bh = (int64_t)B * H;
+    auto wgs = [&](int queries) { return (Tq + queries - 1) / queries * bh; };
+    if (Tk <= 4 * kKTile) {
+        if (wgs(256) >= 512) return {2, 8, false};
+        return {1, wgs(64) <= 256 ? 4 : 8, false};
+    }
+    auto cost = [&](int queries, double rate) { return (double)((wgs(queries) + 255) / 256 * queries) / rate; };
+    const double c64 = d <= 72 ? cost(512, 1014) : INFINITY, c32 = cost(128, 965), c16 = cost(64, d <= 72 ? 733 : 550);
+    if (c64 <= c32 && c64 <= c16) return {4, 8, true};
+    if (c32 > c16) return {1, 4, true};
+    return wgs(128) <= 256 ? AttnVariant{1, 8, true} : AttnVariant{2, 4, true};
+}
+
 int launch_attention(int dtype, AttnArgs a, hipStream_t s) {
     if (a.B <= 0 || a.H <= 0 || a.Tq0 + a.Tq1 <= 0) return BC_OK;
     if (a.Tk0 + a.Tk1 <= 0) return fail(BC_ERR_INVALID_ARG, "attention over zero keys");
@@ -1071,48 +1107,21 @@ int launch_attention(int dtype, AttnArgs a, hipStream_t s) {
     a.scale_log2 = a.q_scaled ? 1.0f : attn_q_scale(a.d);
     prof_begin(PROF_ATTENTION, s, 4.0 * a.B * a.H * (double)(a.Tq0 + a.Tq1) * (double)(a.Tk0 + a.Tk1) * a.d);
     // The direct-to-LDS kernel needs 16-byte aligned Q/K/V rows (checked above).
-    // Up to 256 keys, every key tile is resident in LDS (one load, no barriers
-    // in the key loop): 8 waves of 32 queries when that still leaves two rounds
-    // of 256-query workgroups (PixArt's cross-attention to 120 keys at batch 4:
-    // 35.1 -> 28.7 us in a probe, 59.6 -> 58.5 ms of attention per sampling
-    // run), 4 waves of 16 when those make at most one round (one DiT-XL/2
-    // sample: 6.5 us against 7.4 with 8 waves), else 8 waves of 16 (DiT-XL/2's
-    // self-attention at batch 16: 13.9 us against 17.6 with 4 waves).
-    // Longer sequences, waves over a double buffer: 8 waves of 64 queries
-    // (d <= 72: every K/V fragment read from LDS feeds four MFMAs; at d = 128
-    // they would spill), 4 waves of 32, or 4 of 16; the one whose fullest CU
-    // (rounds of 256 workgroups times queries each) finishes first at the rate
-    // that it reaches on a full grid (4 x 16 x 4096^2 x 72: 1014, 965 and 733
-    // TFLOP/s; 550 for 4 x 16 at d = 128, where two workgroups fill a CU's LDS: 24
-    // heads of 1846^2 71 us against 56 with 4 x 32).  2 x 16 x 2050^2 x 64, unscaled: 4 x 32 queries in 63 us, 4 x 16
-    // in 65, 8 x 32 in 99; 1 x 16 x 1020^2 x 72: 4 x 16 in 16.4 us, 4 x 32 in
-    // 20.1; at d = 128 two 4-wave workgroups a CU, whose barriers do not line
-    // up, ran 24 x 14 566 tokens 6 % faster than one of 8 waves.
-    // Where the 128-query workgroups make at most one round, 8 waves of 16
-    // queries instead of 4 of 32, which would leave one wave on each SIMD (3 x 15
-    // heads of 337^2 x 64: 8.9 us against 10.4; 18 of 1126 x 558 x 72: 13.6
-    // against 15.1; 2 x 19 of 432^2 x 128: 15.7 against 17.3).
     int rc;
     if (dtype == BC_BF16) {
-        const int Tk = a.Tk0 + a.Tk1, Tq = a.Tq0 + a.Tq1;
-        const int64_t bh = (int64_t)a.B * a.H;
-        auto wgs = [&](int queries) { return (Tq + queries - 1) / queries * bh; };
-        if (Tk <= 4 * kKTile) {
-            if (wgs(256) >= 512) rc = run_attention_dma<2, 8, 4, false>(a, a.d, s);
-            else if (wgs(64) <= 256) rc = run_attention_dma<1, 4, 4, false>(a, a.d, s);
+        const AttnVariant v = attention_variant(a.B, a.H, a.Tq0 + a.Tq1, a.Tk0 + a.Tk1, a.d);
+        if (!v.stream) {
+            if (v.qg == 2) rc = run_attention_dma<2, 8, 4, false>(a, a.d, s);
+            else if (v.waves == 4) rc = run_attention_dma<1, 4, 4, false>(a, a.d, s);
             else rc = run_attention_dma<1, 8, 4, false>(a, a.d, s);
+        } else if (v.qg == 4) {
+            rc = a.q_scaled ? run_attention_dma<4, 8, 2, true, true>(a, a.d, s) : run_attention_dma<4, 8, 2>(a, a.d, s);
+        } else if (v.qg == 2) {
+            rc = a.q_scaled ? run_attention_dma<2, 4, 2, true, true>(a, a.d, s) : run_attention_dma<2, 4, 2>(a, a.d, s);
+        } else if (v.waves == 8) {
+            rc = a.q_scaled ? run_attention_dma<1, 8, 2, true, true>(a, a.d, s) : run_attention_dma<1, 8, 2>(a, a.d, s);
         } else {
-            auto cost = [&](int queries, double rate) { return (double)((wgs(queries) + 255) / 256 * queries) / rate; };
-            const double c64 = a.d <= 72 ? cost(512, 1014) : INFINITY, c32 = cost(128, 965),
-                         c16 = cost(64, a.d <= 72 ? 733 : 550);
-            if (c64 <= c32 && c64 <= c16)
-                rc = a.q_scaled ? run_attention_dma<4, 8, 2, true, true>(a, a.d, s) : run_attention_dma<4, 8, 2>(a, a.d, s);
-            else if (c32 <= c16 && wgs(128) <= 256)
-                rc = a.q_scaled ? run_attention_dma<1, 8, 2, true, true>(a, a.d, s) : run_attention_dma<1, 8, 2>(a, a.d, s);
-            else if (c32 <= c16)
-                rc = a.q_scaled ? run_attention_dma<2, 4, 2, true, true>(a, a.d, s) : run_attention_dma<2, 4, 2>(a, a.d, s);
-            else
-                rc = a.q_scaled ? run_attention_dma<1, 4, 2, true, true>(a, a.d, s) : run_attention_dma<1, 4, 2>(a, a.d, s);
+            rc = a.q_scaled ? run_attention_dma<1, 4, 2, true, true>(a, a.d, s) : run_attention_dma<1, 4, 2>(a, a.d, s);
         }
     } else {
         rc = run_attention<float, 1>(a, a.d, s);
@@ -1160,6 +1169,17 @@ int bc_attention_workspace_size(int B, int H, int Tq, int Tk, int d, int dtype, 
     if (!bytes) return fail(BC_ERR_INVALID_ARG, "NULL pointer");
     (void)B; (void)H; (void)Tq; (void)Tk; (void)d; (void)dtype;
     *bytes = 0;   // the kernel reads the [B, T, H, d] layout directly
+    return BC_OK;
+}
+
+int bc_attention_variant(int B, int H, int Tq, int Tk, int d, int* qg, int* waves, int* stream) {
+    clear_error();
+    if (!qg || !waves || !stream) return fail(BC_ERR_INVALID_ARG, "NULL pointer");
+    if (B < 1 || H < 1 || Tq < 1 || Tk < 1 || !attention_supported(d)) return fail(BC_ERR_INVALID_ARG, "attention shape");
+    const AttnVariant v = attention_variant(B, H, Tq, Tk, d);
+    *qg = v.qg;
+    *waves = v.waves;
+    *stream = v.stream ? 1 : 0;
     return BC_OK;
 }
 

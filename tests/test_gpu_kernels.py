@@ -74,7 +74,7 @@ def test_linear_rejects_bad_k(bclib):
     ("bf16", 2, 3, 200, 200, 72), ("bf16", 1, 2, 100, 37, 128), ("bf16", 2, 2, 64, 64, 32),
     ("bf16", 1, 1, 130, 257, 64), ("bf16", 1, 1, 1, 1, 72), ("bf16", 16, 16, 256, 256, 72),
     ("bf16", 1, 2, 1100, 700, 72), ("bf16", 2, 1, 600, 1030, 32), ("bf16", 1, 2, 520, 333, 128),
-    # enough (sample, head) pairs for the 256- and 512-query workgroups
+    # enough (sample, head) pairs for several rounds of 128-query workgroups
     ("bf16", 8, 32, 300, 300, 72), ("bf16", 8, 32, 300, 270, 64), ("bf16", 4, 32, 300, 333, 128),
     # resident key tiles with 32 queries per wave (short key sequences, large grids)
     ("bf16", 8, 32, 300, 120, 72), ("bf16", 8, 32, 300, 200, 128), ("bf16", 8, 32, 260, 256, 32),
@@ -91,10 +91,9 @@ def test_attention(bclib, dt, B, H, Tq, Tk, d):
     assert err <= (1e-2 if dt == "bf16" else 1e-5), err
 
 
-# Pre-scaled queries (the form the blocks' projections write): every key-loop
-# variant, i.e. the resident loop, and the streaming loop with 16, 32 (4-wave
-# workgroups at d = 128, 8-wave otherwise) and 64 queries per wave; at d = 128
-# the last key tile holds 13 keys (333) or 54 (310).
+# Pre-scaled queries (the form the blocks' projections write): the resident
+# loop, and the streaming loop with 16 and 32 queries per wave (64: see
+# ATT_VARIANTS); at d = 128 the last key tile holds 13 keys (333) or 54 (310).
 @pytest.mark.parametrize("B,H,Tq,Tk,d", [
     (16, 16, 256, 256, 72), (1, 2, 100, 37, 128), (1, 2, 1100, 700, 72), (1, 2, 520, 333, 128),
     (2, 1, 600, 1030, 32), (4, 16, 300, 300, 72), (4, 32, 300, 333, 128), (4, 32, 300, 310, 128),
@@ -218,9 +217,9 @@ def test_linear_large_grids(bclib, M, N, K, epi):
     test_linear_small_grids(bclib, "bf16", M, N, K, 0, epi)
 
 
-# The streaming attention's workgroups of 4 waves: 16 and 32 queries per wave by
-# the size of the grid, queries one past a tile, key tiles of one key; and the
-# resident ones of 4 waves (at most 256 workgroups of 64 queries).
+# Small grids of the streaming attention: 16 queries per wave in workgroups of 4
+# or 8 waves, queries one past a tile, key tiles of one key; and the resident
+# workgroups of 4 waves (at most 256 workgroups of 64 queries).
 @pytest.mark.parametrize("prescaled", [False, True])
 @pytest.mark.parametrize("B,H,Tq,Tk,d", [
     (1, 2, 65, 257, 64), (1, 4, 1020, 300, 72), (2, 16, 1025, 321, 64), (1, 24, 1025, 385, 128), (1, 2, 129, 513, 128),
@@ -248,3 +247,19 @@ def test_attention_four_waves(bclib, prescaled, B, H, Tq, Tk, d):
                                    (1840, 3000, 1152), (1840, 3000, 1216), (1840, 3000, 1280), (1840, 3000, 1344)])
 def test_linear_one_round(bclib, M, N, K, epi):
     test_linear_small_grids(bclib, "bf16", M, N, K, 0, epi)
+
+
+# Every workgroup shape of the bf16 attention at every head dim it is built for:
+# (16-query groups per wave, waves, streaming key tiles) and a call that the
+# choice sends there.  Ragged queries and keys; tests/test_attention_variants.py
+# checks on the CPU that these calls still take these shapes.
+ATT_VARIANTS = [((2, 8, 0), (8, 32, 300, 120)), ((1, 4, 0), (1, 3, 65, 70)), ((1, 8, 0), (4, 32, 130, 200)),
+                ((4, 8, 1), (8, 32, 500, 300)), ((2, 4, 1), (2, 24, 1025, 300)), ((1, 8, 1), (1, 24, 1025, 385)),
+                ((1, 4, 1), (1, 2, 65, 257))]
+ATT_VARIANT_CASES = [(v, s + (d,)) for v, s in ATT_VARIANTS for d in (32, 64, 72, 128) if not (v[0] == 4 and d == 128)]
+
+
+@pytest.mark.parametrize("prescaled", [False, True])
+@pytest.mark.parametrize("variant,shape", ATT_VARIANT_CASES)
+def test_attention_variants(bclib, variant, shape, prescaled):
+    test_attention_four_waves(bclib, prescaled, *shape)
