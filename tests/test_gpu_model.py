@@ -69,10 +69,11 @@ def test_dit_block(bclib, name, B, latent):
         assert upd < 1e-4
 
 
-# Samples of at most 256 tokens take the fused QKV projection + attention
-# (one workgroup per sample and head): head dims 72, 64 and 32, a ragged last
-# key tile (196 and 110 tokens), a full one (256), a single token, and 33
-# samples (528 workgroups: more than one round over the CUs).
+# Samples of at most 256 tokens at head dims 72, 64 and 32: 33 samples of 196
+# tokens take the fused QKV projection + attention (one workgroup per sample and
+# head, 528 of them: more than one round over the CUs), the other cases, of at
+# most 1024 rows, the projection and the attention as two kernels (a ragged last
+# key tile, a full one, a single token).
 @pytest.mark.parametrize("hidden,heads,hd,latent,B", [
     (1152, 16, 72, (4, 28, 28), 2), (512, 8, 64, (4, 20, 22), 3), (256, 8, 32, (4, 32, 32), 2),
     (1152, 16, 72, (4, 2, 2), 2), (1152, 16, 72, (4, 28, 28), 33)],
@@ -553,6 +554,14 @@ def test_modulation_linear_widest(bclib, B):
                          ids=["d64_T110_B10", "d32_T256_B5"])
 def test_dit_block_fused_qkv_attention_rows(bclib, hidden, heads, hd, latent, B):
     test_dit_block_fused_qkv_attention(bclib, hidden, heads, hd, latent, B)
+
+
+# The fused kernel on samples that fit one key tile, ragged and full: most of
+# its projection's 256 rows repeat the sample's last one, in both halves.
+@pytest.mark.parametrize("hidden,heads,hd,latent", [(256, 8, 32, (4, 2, 34)), (256, 4, 64, (4, 16, 16)), (576, 8, 72, (4, 2, 34))],
+                         ids=["d32_T17", "d64_T64", "d72_T17"])
+def test_dit_block_fused_qkv_attention_one_tile(bclib, hidden, heads, hd, latent):
+    test_dit_block_fused_qkv_attention(bclib, hidden, heads, hd, latent, 64)
 
 
 # The fused kernel's projection at few and at odd counts of its 64-wide k-steps
