@@ -219,15 +219,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_kernel(GemmArgs g
 // Requires K % 64 == 0 (whole k-steps); rows past M or N are clamped to the
 // last row, so they load valid memory and only feed outputs never stored.
 // ---------------------------------------------------------------------------
-// LDS slot permutation of row r (see above); SW selects among candidate maps.
-template <int SW> __device__ __forceinline__ int swz_of(int row) {
-    if constexpr (SW == 0) return (row >> 1) & 7;
-    else if constexpr (SW == 1) return row & 7;
-    else return 0;
-}
-__device__ __forceinline__ int swz(int row) { return swz_of<0>(row); }
+// LDS slot permutation of row r (see above).
+__device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 
-template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, bool SEG, int SW = 0>
+template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, bool SEG>
 __device__ __forceinline__ void gemm_dma_body(GemmArgs g, const GemmSeg* sg) {
     typedef bf16 T;
     typedef Mma<bf16> MM;
@@ -274,13 +269,13 @@ __device__ __forceinline__ void gemm_dma_body(GemmArgs g, const GemmSeg* sg) {
     for (int o = 0; o < OA; ++o) {
         const int r = (wave * OA + o) * 8 + lrow;
         const int grow = min(bm + r, g.M - 1);
-        srcA[o] = static_cast<const T*>(g.A) + (int64_t)grow * g.lda + ((lslot ^ swz_of<SW>(r)) * 8);
+        srcA[o] = static_cast<const T*>(g.A) + (int64_t)grow * g.lda + ((lslot ^ swz(r)) * 8);
     }
 #pragma unroll
     for (int o = 0; o < OB; ++o) {
         const int r = (wave * OB + o) * 8 + lrow;
         const int grow = min(bn + r, g.N - 1);
-        srcB[o] = static_cast<const T*>(g.W) + (int64_t)grow * g.ldw + ((lslot ^ swz_of<SW>(r)) * 8);
+        srcB[o] = static_cast<const T*>(g.W) + (int64_t)grow * g.ldw + ((lslot ^ swz(r)) * 8);
     }
     auto issue = [&](int kt, int buf) {
         const int k0 = kt * BK;
@@ -318,12 +313,12 @@ __device__ __forceinline__ void gemm_dma_body(GemmArgs g, const GemmSeg* sg) {
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
                 const int r = wm * WM + i * 16 + frow;
-                af[i] = MM::load(a + r * BK + ((c ^ swz_of<SW>(r)) * 8));
+                af[i] = MM::load(a + r * BK + ((c ^ swz(r)) * 8));
             }
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 const int r = wn * WN + j * 16 + frow;
-                bfr[j] = MM::load(b + r * BK + ((c ^ swz_of<SW>(r)) * 8));
+                bfr[j] = MM::load(b + r * BK + ((c ^ swz(r)) * 8));
             }
 #pragma unroll
             for (int i = 0; i < TM; ++i)
@@ -1044,9 +1039,9 @@ static void launch_wide(const GemmArgs& g, hipStream_t s) {
     launch_k(gemm_wide_kernel<EPI, BM, BN, WAVES_M, WAVES_N>, dim3(tiles), dim3(64 * WAVES_M * WAVES_N), s, g);
 }
 
-template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int SW = 0>
+template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dma_kernel(GemmArgs g) {
-    gemm_dma_body<EPI, BM, BN, WAVES_M, WAVES_N, STAGES, false, SW>(g, nullptr);
+    gemm_dma_body<EPI, BM, BN, WAVES_M, WAVES_N, STAGES, false>(g, nullptr);
 }
 
 template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
@@ -1054,10 +1049,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dma_seg_kernel(Ge
     gemm_dma_body<EPI, BM, BN, WAVES_M, WAVES_N, STAGES, true>(g, &sg);
 }
 
-template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int SW = 0>
+template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
 static void launch_dma(const GemmArgs& g, hipStream_t s) {
     const unsigned tiles = (unsigned)(((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN));
-    launch_k(gemm_dma_kernel<EPI, BM, BN, WAVES_M, WAVES_N, STAGES, SW>, dim3(tiles), dim3(64 * WAVES_M * WAVES_N), s, g);
+    launch_k(gemm_dma_kernel<EPI, BM, BN, WAVES_M, WAVES_N, STAGES>, dim3(tiles), dim3(64 * WAVES_M * WAVES_N), s, g);
 }
 
 // ---------------------------------------------------------------------------
@@ -1065,18 +1060,21 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
 //
 // With few rows the tiles above leave most CUs idle and walk all of K as one
 // serial chain of loads, barrier and MFMAs (M = 256, N = 1152, K = 4608: 16
-// workgroups, 72 steps, 46 us).  Here a tile is small, and each of the WK waves
-// accumulates all of it over k-steps of its own (wave w takes steps w, w + WK,
-// ...; a step is 128 bytes of every operand row), loaded straight into a ring
-// of S stages that only this wave uses: the loads of the waves keep each other
-// company, and no barrier stops them until the partial tiles meet in LDS, in a
-// fixed order, for the epilogue.  What bounds it is what a CU's loads deliver,
-// about 64 GB/s, so the time is close to (rounds of workgroups) (BM + BN) K
-// bytes over that: 10.6 us for the shape above.  (Fragments loaded from global
-// memory straight into registers, without the trip through LDS, ran at a third
-// of that: the 16 lanes of a fragment row fetch from 16 rows, 16 bytes each.)
+// workgroups, 72 steps, 46 us).  Here a tile is small, and each of the 8 waves
+// accumulates all of it over k-steps of its own (wave w takes steps w, w + 8,
+// ...; a step is 128 bytes of every operand row), loaded straight into a stage
+// that only this wave uses and loaded again as soon as it has been read: the
+// loads of the waves keep each other company, and no barrier stops them until
+// the partial tiles meet in LDS, in a fixed order, for the epilogue.  What
+// bounds it is what a CU's loads deliver, about 64 GB/s, so the time is close to
+// (rounds of workgroups) (BM + BN) K bytes over that: 10.6 us for the shape
+// above.  (Fragments loaded from global memory straight into registers, without
+// the trip through LDS, ran at a third of that: the 16 lanes of a fragment row
+// fetch from 16 rows, 16 bytes each.)
 // Any N and alignment of the outputs (vec: 4-column accesses are possible).
 // ---------------------------------------------------------------------------
+constexpr int kKsWaves = 8;
+
 template <typename T> struct KsMma;
 template <> struct KsMma<bf16> {
     __device__ static __forceinline__ f32x4 mma(const u32x4& w, const u32x4& a, const f32x4& c) {
@@ -1147,19 +1145,19 @@ __device__ __forceinline__ void finish4(const GemmArgs& g, int row, int col, con
     }
 }
 
-template <typename T_, int EPI, int TM, int TN, int WK, int S>
-__global__ __launch_bounds__(64 * WK) void gemm_ksplit_kernel(GemmArgs g, int vec) {
+template <typename T_, int EPI, int TM, int TN>
+__global__ __launch_bounds__(64 * kKsWaves) void gemm_ksplit_kernel(GemmArgs g, int vec) {
     typedef elem_t<T_> T;
     typedef KsMma<T> MM;
-    constexpr int BM = 16 * TM, BN = 16 * TN, PITCH = BN + 4;
+    constexpr int WK = kKsWaves, BM = 16 * TM, BN = 16 * TN, PITCH = BN + 4;
     constexpr int BK = 128 / (int)sizeof(T);               // k per step: 128 bytes of every row
     constexpr int Q = (BM + BN) / 8;                       // wave-wide loads per step
-    constexpr int STAGE = (BM + BN) * 128, RING = S * STAGE;
-    // Partial tiles held in LDS at once: all of them, or half (a quarter) of them.
+    constexpr int STAGE = (BM + BN) * 128;
+    // Partial tiles held in LDS at once: all of them, or half of them.
     constexpr int SLOT = BM * PITCH;
-    constexpr int NS = WK * SLOT * 4 <= WK * RING ? WK : WK * SLOT * 2 <= WK * RING ? WK / 2 : WK / 4;
-    static_assert(NS >= 1 && NS * SLOT * 4 <= WK * RING && WK * RING <= 160 * 1024, "LDS");
-    __shared__ __attribute__((aligned(1024))) char sm[WK * RING];
+    constexpr int NS = SLOT * 4 <= STAGE ? WK : WK / 2;
+    static_assert(NS * SLOT * 4 <= WK * STAGE && WK * STAGE <= 160 * 1024, "LDS");
+    __shared__ __attribute__((aligned(1024))) char sm[WK * STAGE];
     typedef __attribute__((address_space(3))) const char lds_char;
     typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1179,42 +1177,38 @@ __global__ __launch_bounds__(64 * WK) void gemm_ksplit_kernel(GemmArgs g, int ve
         voff[q] = r < BM ? (uint32_t)(min(bm + r, g.M - 1) - bm) * (uint32_t)(g.lda * sizeof(T)) + ch
                          : (uint32_t)(min(bn + r - BM, g.N - 1) - bn) * (uint32_t)(g.ldw * sizeof(T)) + ch;
     }
-    const uint32_t ring = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_char*)sm + wave * RING);
-    // Step i of this wave is k-step wave + WK i, in stage i % S of its ring.
+    const uint32_t stage = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_char*)sm + wave * STAGE);
+    // Step i of this wave is k-step wave + WK i.
     const int nk = g.K / BK;
     const int n = nk > wave ? (nk - wave + WK - 1) / WK : 0;
-    auto issue = [&](int i, int stage) __attribute__((always_inline)) {
+    auto issue = [&](int i) __attribute__((always_inline)) {
         const int64_t k = (int64_t)(wave + WK * i) * 128;
 #pragma unroll
-        for (int q = 0; q < Q; ++q) dma16s((8 * q < BM ? baseA : baseW) + k, voff[q], ring + stage * STAGE + q * 1024);
+        for (int q = 0; q < Q; ++q) dma16s((8 * q < BM ? baseA : baseW) + k, voff[q], stage + q * 1024);
     };
     lds_char* frag[2];
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk)
-        frag[kk] = (lds_char*)sm + wave * RING + r16 * 128 + ((kk * 4 + grp) ^ ((r16 >> 1) & 7)) * 16;
+        frag[kk] = (lds_char*)sm + wave * STAGE + r16 * 128 + ((kk * 4 + grp) ^ ((r16 >> 1) & 7)) * 16;
     f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int p = 0; p < S; ++p)
-        if (p < n) issue(p, p);
-    int stage = 0;
+    if (n > 0) issue(0);
     for (int i = 0; i < n; ++i) {
-        wait_groups<Q, S - 1>(n - 1 - i);       // step i has landed; later ones may be on their way
+        wait_vmcnt<0>();       // step i has landed
         asm volatile("" ::: "memory");
         u32x4 fa[2][TM], fw[2][TN];
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
-            for (int j = 0; j < TN; ++j) fw[kk][j] = *(lds_u32x4*)(frag[kk] + stage * STAGE + (BM + 16 * j) * 128);
+            for (int j = 0; j < TN; ++j) fw[kk][j] = *(lds_u32x4*)(frag[kk] + (BM + 16 * j) * 128);
 #pragma unroll
-            for (int m = 0; m < TM; ++m) fa[kk][m] = *(lds_u32x4*)(frag[kk] + stage * STAGE + 16 * m * 128);
+            for (int m = 0; m < TM; ++m) fa[kk][m] = *(lds_u32x4*)(frag[kk] + 16 * m * 128);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // read before the stage is filled again
-        if (i + S < n) issue(i + S, stage);
-        stage = stage + 1 == S ? 0 : stage + 1;
+        if (i + 1 < n) issue(i + 1);
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
@@ -1222,9 +1216,9 @@ __global__ __launch_bounds__(64 * WK) void gemm_ksplit_kernel(GemmArgs g, int ve
 #pragma unroll
                 for (int j = 0; j < TN; ++j) acc[m][j] = MM::mma(fw[kk][j], fa[kk][m], acc[m][j]);
     }
-    __syncthreads();      // the partial tiles take the rings' place
+    __syncthreads();      // the partial tiles take the stages' place
     float* red = reinterpret_cast<float*>(sm);
-    // Partial tiles to LDS: the last NS waves store, the groups of NS before them add.
+    // Partial tiles to LDS: the last NS waves store, the NS before them (if any) add.
 #pragma unroll
     for (int r = WK / NS - 1; r >= 0; --r) {
         if (wave / NS == r) {
@@ -1251,10 +1245,10 @@ __global__ __launch_bounds__(64 * WK) void gemm_ksplit_kernel(GemmArgs g, int ve
     }
 }
 
-template <typename T, int EPI, int TM, int TN, int WK, int S>
+template <typename T, int EPI, int TM, int TN>
 static void launch_ksplit(const GemmArgs& g, bool vec, hipStream_t s) {
     const unsigned tiles = (unsigned)(((g.M + 16 * TM - 1) / (16 * TM)) * ((g.N + 16 * TN - 1) / (16 * TN)));
-    launch_k(gemm_ksplit_kernel<tag_t<T>, EPI, TM, TN, WK, S>, dim3(tiles), dim3(64 * WK), s, g, vec ? 1 : 0);
+    launch_k(gemm_ksplit_kernel<tag_t<T>, EPI, TM, TN>, dim3(tiles), dim3(64 * kKsWaves), s, g, vec ? 1 : 0);
 }
 
 // Whether every column index, stride and boundary of the epilogue is a
@@ -1532,8 +1526,8 @@ static bool run_ksplit(const GemmArgs& g, hipStream_t s) {
     const bool vec = vec4_ok(g, EPI);
     if constexpr (sizeof(T) == 4) {
         if (tiles(32, 48) > 0x7fffffff) return false;
-        if (tiles(16, 16) <= 4 * 256) launch_ksplit<T, EPI, 1, 1, 8, 1>(g, vec, s);
-        else launch_ksplit<T, EPI, 2, 3, 8, 1>(g, vec, s);
+        if (tiles(16, 16) <= 4 * 256) launch_ksplit<T, EPI, 1, 1>(g, vec, s);
+        else launch_ksplit<T, EPI, 2, 3>(g, vec, s);
         return true;
     } else {
         auto rows = [&](int bm, int bn) { return (tiles(bm, bn) + 255) / 256 * (bm + bn); };
@@ -1543,10 +1537,10 @@ static bool run_ksplit(const GemmArgs& g, hipStream_t s) {
             if (r[i] < r[best]) best = i;
         if (r[best] > 240 || tiles(128, 144) > 256) return false;
         switch (best) {
-            case 0: launch_ksplit<T, EPI, 2, 3, 8, 1>(g, vec, s); break;
-            case 1: launch_ksplit<T, EPI, 4, 3, 8, 1>(g, vec, s); break;
-            case 2: launch_ksplit<T, EPI, 4, 4, 8, 1>(g, vec, s); break;
-            default: launch_ksplit<T, EPI, 4, 5, 8, 1>(g, vec, s); break;
+            case 0: launch_ksplit<T, EPI, 2, 3>(g, vec, s); break;
+            case 1: launch_ksplit<T, EPI, 4, 3>(g, vec, s); break;
+            case 2: launch_ksplit<T, EPI, 4, 4>(g, vec, s); break;
+            default: launch_ksplit<T, EPI, 4, 5>(g, vec, s); break;
         }
         return true;
     }
