@@ -211,12 +211,16 @@ def group_launches(records, cfg):
     return groups
 
 
-# kernel-name prefix of a profiled class's launches (the gated epilogue is template argument 2)
+# kernel-name prefixes of a profiled class's launches, by the epilogue's template argument (gated: 2)
+def _gemm_kernels(epi):
+    return (f"void bc::gemm_wide_kernel<{epi},", f"void bc::gemm_phase_kernel<{epi},",
+            f"void bc::gemm_phase_pair_kernel<{epi}>", f"void bc::gemm_mid_kernel<{epi},",
+            f"void bc::gemm_ksplit_kernel<bf16_tag, {epi},")
+
+
 CLASS_KERNEL = {"attention": ("void bc::attention_dma_kernel<",),
-                "gemm_gated": ("void bc::gemm_wide_kernel<2,", "void bc::gemm_phase_kernel<2,", "void bc::gemm_phase_pair_kernel<2>", "void bc::gemm_mid_kernel<2,"),
-                "gemm_down": ("void bc::gemm_wide_kernel<2,", "void bc::gemm_phase_kernel<2,", "void bc::gemm_phase_pair_kernel<2>", "void bc::gemm_mid_kernel<2,"),
-                "gemm_gelu": ("void bc::gemm_wide_kernel<0,", "void bc::gemm_phase_kernel<0,", "void bc::gemm_phase_pair_kernel<0>", "void bc::gemm_mid_kernel<0,"),
-                "gemm_bias": ("void bc::gemm_wide_kernel<0,", "void bc::gemm_phase_kernel<0,", "void bc::gemm_phase_pair_kernel<0>", "void bc::gemm_mid_kernel<0,")}
+                "gemm_gated": _gemm_kernels(2), "gemm_down": _gemm_kernels(2),
+                "gemm_gelu": _gemm_kernels(0), "gemm_bias": _gemm_kernels(0)}
 
 
 def loop_traffic(workload, g, src):
@@ -261,10 +265,12 @@ def grid_fits(kernel, grid_threads, g):
     if "gemm_phase" in kernel:   # 256 x 256 (pairs too) or 256 x 288 tiles of 512 threads
         bn = 288 if len(args) > 1 and args[1] == "3" else 256
         return grid_threads == -(-g["shape"][0] // 256) * -(-g["shape"][1] // bn) * 512
+    if "gemm_ksplit" in kernel:  # tiles of 16 TM x 16 TN, 512 threads
+        tm, tn = int(args[2]), int(args[3])
+        return grid_threads == -(-g["shape"][0] // (16 * tm)) * -(-g["shape"][1] // (16 * tn)) * 512
     bm, bn, wm, wn = int(args[1]), int(args[2]), int(args[3]), int(args[4])
-    kg = int(args[7]) if len(args) > 7 else 1
     M, N = g["shape"][0], g["shape"][1]
-    return grid_threads == -(-M // bm) * -(-N // bn) * 64 * wm * wn * kg
+    return grid_threads == -(-M // bm) * -(-N // bn) * 64 * wm * wn
 
 
 def roofline_of(g, tag=None, src=None, workload=None):

@@ -59,3 +59,14 @@ def test_grid_fits_gemm_tiles():
     kernel = "void bc::gemm_wide_kernel<2, 128, 144, 4, 4, 4, 64, 1, 1>(bc::GemmArgs)"
     assert bench.grid_fits(kernel, 32 * 8 * 64 * 16, g)
     assert not bench.grid_fits(kernel, 32 * 8 * 64 * 12, g)
+
+
+def test_class_kernels_know_the_k_split():
+    """A k-split launch belongs to its class by its epilogue, and its grid to its tile."""
+    gated = "void bc::gemm_ksplit_kernel<bf16_tag, 2, 4, 3>(bc::GemmArgs, int)"
+    plain = "void bc::gemm_ksplit_kernel<bf16_tag, 0, 4, 5>(bc::GemmArgs, int)"
+    assert gated.startswith(bench.CLASS_KERNEL["gemm_down"]) and not gated.startswith(bench.CLASS_KERNEL["gemm_gelu"])
+    assert plain.startswith(bench.CLASS_KERNEL["gemm_bias"]) and not plain.startswith(bench.CLASS_KERNEL["gemm_gated"])
+    assert bench.grid_fits(gated, 4 * 24 * 512, {"shape": [250, 1152, 4608]})
+    assert not bench.grid_fits(gated, 4 * 24 * 512, {"shape": [260, 1152, 4608]})
+    assert bench.grid_fits(plain, 4 * 44 * 512, {"shape": [256, 3456, 1152]})
