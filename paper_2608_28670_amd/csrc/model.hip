@@ -120,13 +120,27 @@ static int qproj(int dt, const void* A, int64_t lda, const void* W, const void* 
     return launch_gemm(dt, BC_EPI_BIAS, g, s);
 }
 
-// Rows up to which the QKV projection and the attention of short sequences run
-// as two kernels.  The fused kernel has one workgroup per (sample, head), each
-// with all of the projection's k-steps, so its time does not fall below that of
-// one round: 33 us for one DiT-XL/2 sample (16 workgroups), where the k-split
-// projection and the attention take 9 + 7 us; with four samples (1024 rows) 19 +
-// 8 against 33, with eight about 30 + 9 against 35.
-constexpr int kFusedQkvRows = 1024;
+// Whether a block of short samples runs its QKV projection and attention in the
+// fused kernel rather than as two.  The fused kernel has one workgroup per
+// (sample, head), each with all of the projection's k-steps over 256 rows,
+// whatever the sample's length: the time of its rounds goes with D alone, that
+// of the separate projection with rows x D x D.  One DiT-XL/2 sample: 33 us (16
+// workgroups) where the k-split projection and the attention take 9 + 7.  Whole
+// blocks of up to 1024 rows (us, fused / two kernels):
+//   d = 72: 4 x 256 tokens of 1152 102 / 96, of 2304 284 / 288;
+//   d = 64: 4 x 256 of 1024 88 / 83, of 2048 219 / 218, of 3072 375 / 428, 2 x 256
+//     of 4096 415 / 408;
+//   d = 32 (half the columns per workgroup): 2 x 256 of 512 42.1 / 40.3, of 1024
+//     71.3 / 72.0, 5 x 100 of 1024 68.8 / 71.4, 8 x 100 of 768 59.9 / 64.3, 4 x 256
+//     of 1024 80 / 85, 1 x 256 of 2048 125 / 122; two rounds, 12 x 64 of 1024, 86 / 80.
+// Above 1024 rows (DiT-XL/2's width): 8 x 256 149 / 164, 16 x 128 149 / 165, 16 x
+// 196 174 / 189, 16 x 256 185 / 205; shorter samples would be better off as two
+// kernels there too (9 x 128 118 / 114, 16 x 72 121 / 114, 32 x 65 182 / 161, 64 x
+// 17 198 / 117), which this rule leaves out.
+static bool fused_qkv_pays(int B, int H, int64_t rows, int head_dim, int D) {
+    if (rows > 1024) return true;
+    return rows > 256 && (int64_t)B * H <= 256 && rows * D >= (head_dim == 32 ? 480 : 2200) * 1024;
+}
 
 // One DiT or PixArt block on x [B*T, D] (fp32).  mod: [B, >= 6D] fp32 rows
 // ld_mod apart, ordered (shift1, scale1, gate1, shift2, scale2, gate2).
@@ -146,7 +160,7 @@ static int dit_block(const bc_block_desc& d, const bc_block_weights& w, float* x
     a.o0 = a.o1 = bb.attn; a.ldo = D;
     a.B = d.B; a.H = d.heads; a.d = d.head_dim;
     auto al = [](const void* p, int n) { return reinterpret_cast<uintptr_t>(p) % n == 0; };
-    if (M > kFusedQkvRows && qkv_attention_supported(dt, T, d.head_dim, D) && d.heads * d.head_dim == D &&
+    if (fused_qkv_pays(d.B, d.heads, M, d.head_dim, D) && qkv_attention_supported(dt, T, d.head_dim, D) && d.heads * d.head_dim == D &&
         al(sw.w_qkv, 16) && al(sw.b_qkv, 8)) {
         // Short sequences (DiT-XL/2's 256 tokens): the QKV projection and the
         // self-attention of a (sample, head) in one workgroup, Q, K and V in LDS.

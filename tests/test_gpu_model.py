@@ -573,6 +573,34 @@ def test_dit_block_fused_qkv_attention_steps(bclib, hidden, heads, hd):
     test_dit_block_fused_qkv_attention(bclib, hidden, heads, hd, (4, 20, 22), 10)
 
 
+# Which blocks of short samples take the fused kernel (told by the work that the
+# attention launch records): above 1024 rows, or one round of workgroups whose
+# projection is large enough; d = 32 from a smaller one on.
+@pytest.mark.parametrize("B,T,heads,hd,fused", [
+    (5, 256, 8, 72, True), (4, 256, 16, 64, False), (4, 256, 48, 64, True), (4, 256, 32, 32, True), (5, 100, 32, 32, True),
+    (2, 256, 16, 32, False), (12, 64, 32, 32, False), (1, 256, 64, 32, False)])
+def test_dit_block_fused_choice(bclib, B, T, heads, hd, fused):
+    D, F = heads * hd, 64
+    g = torch.Generator(device=DEV)
+    g.manual_seed(D + B)
+
+    def rnd(*s, scale=1.0):
+        return torch.empty(s, device=DEV).normal_(0.0, scale, generator=g)
+
+    shapes = {"w_mod": (6 * D, D), "b_mod": (6 * D,), "w_qkv": (3 * D, D), "b_qkv": (3 * D,), "w_o": (D, D), "b_o": (D,),
+              "w_fc1": (F, D), "b_fc1": (F,), "w_fc2": (D, F), "b_fc2": (D,)}
+    w = bclib.block_weights({k: rnd(*s, scale=0.02).bfloat16() for k, s in shapes.items()})
+    desc = bclib.block_desc(bclib.BLOCK_DIT, B, T, D, heads, hd, F, bclib.BF16)
+    ws = torch.empty(bclib.block_workspace_size(desc), dtype=torch.uint8, device=DEV)
+    x, c = rnd(B, T, D), rnd(B, D)
+    bclib.profile_enable(bclib.PROF_ATTENTION, 8)
+    bclib.dit_block_forward(desc, w, x, c, ws)
+    torch.cuda.synchronize()
+    _, work = bclib.profile_records(bclib.PROF_ATTENTION, 8)
+    attention, projection = 4.0 * B * heads * T * T * hd, 6.0 * B * T * D * D
+    assert list(work) == [attention + (projection if fused else 0.0)]
+
+
 # The LayerNorm's rows per wave: one up to 2048 rows, two above.
 @pytest.mark.parametrize("latent,B", [((4, 32, 32), 8), ((4, 10, 82), 10)], ids=["rows2048", "rows2050"])
 def test_dit_block_layernorm_rows(bclib, latent, B):
