@@ -638,8 +638,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_wide_kernel(GemmA
 // 12 288 x 3072 GELU 921 -> 825, 14 566 x 3072 x 15 360 gated 1266 -> 1070,
 // 14 310 x 3072 x 3072 gated 307 -> 276; with 256 x 288 tiles 16 384 x 1152 x
 // 4608 gated 172 -> 155, 16 384 x 4608 x 1152 GELU 172 -> 169.  What bounds it
-// now: the MFMAs are busy 0.67 to 0.78 of the cycles, at the 1.8 to 1.9 GHz that
-// the card's power leaves them.
+// now: the MFMAs are busy 0.65 to 0.67 of a video GEMM's cycles (counters, with
+// prologue and epilogue), at the 1.8 to 1.9 GHz that the card's power leaves
+// them; at K = 1152, where every round has 18 steps, 0.35 to 0.42.
 // (32 x 32 x 16 MFMAs in the same phases: 10 % slower, two accumulators per
 // phase being too short a chain; s_setprio around the MFMAs, or the reads all
 // ahead of them: 3 to 8 % slower.)
@@ -963,7 +964,7 @@ __device__ __forceinline__ void gemm_phase_body(const GemmArgs& g, int tile) {
             }
         }
     } else {
-        // The bias kind.  bf16: as in gemm_wide_body the finished tile goes
+        // The bias kind.  bf16: as in gemm_wide_kernel the finished tile goes
         // through LDS, row-major, and leaves as consecutive 16-byte chunks of
         // its rows.  fp32: straight from the accumulators.
         bf16* so = reinterpret_cast<bf16*>(sm);
@@ -1494,7 +1495,7 @@ static int phase_parts(const GemmArgs& g) {
 //   * at least one full round of 256 x 288 tiles over the 256 CUs: the phased
 //     kernel;
 //   * N a multiple of 432 with at least one round of 128 x 432 tiles (the
-//     DiT-XL/2 QKV projection: exactly 256): 2 x 4 waves of 64 x 112 / 64 x 96;
+//     DiT-XL/2 QKV projection: exactly 256): 4 x 3 waves of 32 x 144;
 //   * at most 256 tiles of 128 x 144 (the N = 1152 projections at M = 4096) and
 //     K >= 1024: those (M = 4096, N = 1152, K = 1152: 20.0 us against 24.8 with
 //     128 x 128 tiles; M = 3000, K = 768: 15.0 against 12.6);
