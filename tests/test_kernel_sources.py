@@ -3,6 +3,7 @@ to, that a run cannot show reliably (CPU)."""
 import glob
 import os
 import re
+from concurrent.futures import ThreadPoolExecutor
 
 import pytest
 
@@ -62,13 +63,22 @@ def _listing(source, tmp):
 
 
 @pytest.fixture(scope="module")
-def ops_listing(tmp_path_factory):
-    return _listing("ops.hip", tmp_path_factory.mktemp("ops"))
+def listings(tmp_path_factory):
+    """The sources with direct-to-LDS loads, compiled side by side."""
+    tmp = tmp_path_factory.mktemp("listings")
+    names = ("gemm.hip", "attention.hip", "ops.hip")
+    with ThreadPoolExecutor(len(names)) as ex:
+        return dict(zip(names, ex.map(lambda n: _listing(n, tmp), names)))
 
 
 @pytest.fixture(scope="module")
-def attention_listing(tmp_path_factory):
-    return _listing("attention.hip", tmp_path_factory.mktemp("attention"))
+def ops_listing(listings):
+    return listings["ops.hip"]
+
+
+@pytest.fixture(scope="module")
+def attention_listing(listings):
+    return listings["attention.hip"]
 
 
 def _template_args(name, kernel):
@@ -140,3 +150,37 @@ def test_attention_stores_its_rows_without_branches(attention_listing):
         stores = [c.split()[0] for c in k.code if c.startswith("global_store")]
         assert stores == ["global_store_dwordx2"] * (t[1] * -(-t[0] // 16)), (name, stores)
     assert found >= 30
+
+
+def _sgprs(text):
+    out = set()
+    for m in re.finditer(r"\bs\[(\d+):(\d+)\]|\bs(\d+)\b", text):
+        out |= {int(m.group(3))} if m.group(3) else set(range(int(m.group(1)), int(m.group(2)) + 1))
+    return out
+
+
+def test_lds_loads_wait_for_their_base(listings):
+    """A vector memory instruction may read a scalar register that a vector
+    instruction wrote (a base made uniform by v_readfirstlane) five wait states
+    later at the earliest.  The compiler sees to it for its own instructions,
+    not inside inline assembly, so the compiled code is looked at."""
+    loads = 0
+    for kernels in listings.values():
+        for name, k in kernels.items():
+            state, written = 0, {}          # wait states passed, scalar register -> state after its vector write
+            for c in k.code:
+                op, _, args = c.partition(" ")
+                if c.endswith(":"):
+                    continue
+                if op.startswith("global_load_lds"):
+                    loads += 1
+                    for r in _sgprs(args):
+                        assert state - written.get(r, -5) >= 5, (name, c)
+                state += 1 + (int(args, 0) if op == "s_nop" else 0)
+                if op.startswith("v_"):
+                    for r in _sgprs(args.split(",")[0]):
+                        written[r] = state
+                elif op.startswith("s_"):
+                    for r in _sgprs(args.split(",")[0]):
+                        written.pop(r, None)
+    assert loads > 1000
