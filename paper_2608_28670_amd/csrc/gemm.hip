@@ -445,7 +445,8 @@ __device__ __forceinline__ void epilogue_t(const GemmArgs& g, const f32x4 (&acc)
     }
 }
 
-template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N>
+// AHEAD (gated epilogue through LDS): when the residual is read, see there.
+template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, bool AHEAD = false>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_wide_kernel(GemmArgs g) {
     typedef bf16 T;
     typedef Mma<bf16> MM;
@@ -539,16 +540,18 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_wide_kernel(GemmA
     if constexpr (STAGE_GATED) {
         // The tile goes through LDS as fp32 rows, and all waves then apply the
         // gated residual to whole rows, reading the residual and gate and
-        // writing the stream as consecutive 16-byte chunks.  All of a thread's
-        // residual is requested first: the stream is updated in place, so no
-        // load is moved over a store by itself.
+        // writing the stream as consecutive 16-byte chunks.  The residual is read
+        // where it is added; AHEAD: all of a thread's before the LDS passes (the
+        // stream is updated in place, so no load is moved over a store by itself).
         constexpr int C4 = BN / 4, IT = BM * C4 / NT;         // 4-column chunks per tile row, and per thread
         static_assert(IT * NT == BM * C4, "chunks per thread");
-        f32x4 rv[IT];
+        f32x4 rv[AHEAD ? IT : 1];
+        if constexpr (AHEAD) {
 #pragma unroll
-        for (int t = 0; t < IT; ++t) {
-            const int q = tid + NT * t, row = min(bm + q / C4, g.M - 1), col = min(bn + q % C4 * 4, g.N - 4);
-            rv[t] = *reinterpret_cast<const f32x4*>(e.res + (int64_t)row * e.ldr + col);
+            for (int t = 0; t < IT; ++t) {
+                const int q = tid + NT * t, row = min(bm + q / C4, g.M - 1), col = min(bn + q % C4 * 4, g.N - 4);
+                rv[t] = *reinterpret_cast<const f32x4*>(e.res + (int64_t)row * e.ldr + col);
+            }
         }
         float* ft = reinterpret_cast<float*>(sm);
         __syncthreads();   // every wave is done with the stage buffers
@@ -561,8 +564,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_wide_kernel(GemmA
 #pragma unroll
         for (int t = 0; t < IT; ++t) {
             const int q = tid + NT * t, lr = q / C4, lc = q % C4 * 4;
-            if (bm + lr < g.M && bn + lc < g.N)
-                gate_res4(g, bm + lr, bn + lc, *reinterpret_cast<const f32x4*>(ft + lr * FPITCH + lc), rv[t]);
+            const int row = bm + lr, col = bn + lc;
+            if (row >= g.M || col >= g.N) continue;
+            if constexpr (!AHEAD) rv[0] = *reinterpret_cast<const f32x4*>(e.res + (int64_t)row * e.ldr + col);
+            gate_res4(g, row, col, *reinterpret_cast<const f32x4*>(ft + lr * FPITCH + lc), rv[AHEAD ? t : 0]);
         }
         return;
     }
@@ -1034,10 +1039,10 @@ static void launch_phase(const GemmArgs& g, hipStream_t s) {
     launch_k(gemm_phase_kernel<EPI, NP>, dim3((unsigned)(((g.M + 255) / 256) * ((g.N + BN - 1) / BN))), dim3(512), s, g);
 }
 
-template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N>
+template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, bool AHEAD = false>
 static void launch_wide(const GemmArgs& g, hipStream_t s) {
     const unsigned tiles = (unsigned)(((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN));
-    launch_k(gemm_wide_kernel<EPI, BM, BN, WAVES_M, WAVES_N>, dim3(tiles), dim3(64 * WAVES_M * WAVES_N), s, g);
+    launch_k(gemm_wide_kernel<EPI, BM, BN, WAVES_M, WAVES_N, AHEAD>, dim3(tiles), dim3(64 * WAVES_M * WAVES_N), s, g);
 }
 
 template <int EPI, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
@@ -1501,7 +1506,14 @@ static int phase_parts(const GemmArgs& g) {
 //     128 x 128 tiles; M = 3000, K = 768: 15.0 against 12.6);
 //   * at most 256 tiles of 128 x 192 and K >= 1152: those (M = 2048, N = 3072, K =
 //     1536: 28.5 us against 31.3; equal at K = 1152, 21.4 against 20.6 at 1024);
-//   * otherwise 128 x 128 (16 waves of 32 x 32, two workgroups per CU).
+//   * otherwise 128 x 128 (16 waves of 32 x 32, two workgroups per CU).  Gated: the
+//     two cover each other's epilogue, and a residual requested ahead of it cost
+//     up to a tenth (16 000 x 384 x 384 16.4 us against 14.9, 8192 x 768 x 768 20.9
+//     against 20.0, 3500 x 2304 x 768 24.3 against 22.6); only where few workgroups
+//     are left for a last round, alone on their CUs, is it read ahead (528 tiles,
+//     4100 x 2048 x 2048, 59.2 us against 62.1; 564, 12 000 x 768 x 768, 35.2
+//     against 37.7; 624, 9900 x 1000 x 640, 33.9 against 36.7; 768 of them 44.2
+//     against 43.7; and at K = 256, 549 tiles, 22.5 against 21.5).
 // Other bf16 operands take the direct-to-LDS kernel with the scalar
 // epilogue, or the register-staged kernel, as does fp32 with K % 32 != 0.
 // Before all of these, grids too small for them go to the k-split kernel.
@@ -1569,6 +1581,8 @@ static int run_gemm(const GemmArgs& g, hipStream_t s) {
                 launch_mid<EPI, 144>(g, s);
             } else if (tiles192 <= 256 && mid && g.K >= 1152) {
                 launch_mid<EPI, 192>(g, s);
+            } else if (EPI == BC_EPI_GATE_RES && g.K >= 512 && tiles128 > 512 && (tiles128 - 1) % 512 < 128) {
+                launch_wide<EPI, 128, 128, 4, 4, EPI == BC_EPI_GATE_RES>(g, s);
             } else {
                 launch_wide<EPI, 128, 128, 4, 4>(g, s);
             }

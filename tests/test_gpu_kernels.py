@@ -249,6 +249,15 @@ def test_linear_one_round(bclib, M, N, K, epi):
     test_linear_small_grids(bclib, "bf16", M, N, K, 0, epi)
 
 
+# 128 x 128 tiles of more than one round: a last round of few workgroups, whose
+# gated epilogue reads the residual ahead (544 tiles, K = 512; not at 448), and a
+# fuller one (720 tiles); ragged rows and columns.
+@pytest.mark.parametrize("epi", ["bias", "gelu", "gate"])
+@pytest.mark.parametrize("M,N,K", [(3990, 2120, 512), (3990, 2120, 448), (5690, 2040, 512)])
+def test_linear_last_round(bclib, M, N, K, epi):
+    test_linear_small_grids(bclib, "bf16", M, N, K, 0, epi)
+
+
 # Every workgroup shape of the bf16 attention at every head dim it is built for:
 # (16-query groups per wave, waves, streaming key tiles) and a call that the
 # choice sends there.  Ragged queries and keys; tests/test_attention_variants.py
