@@ -741,6 +741,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
 
     f32x4 o[QG][S::DV / 16], osum[QG];
     float m_run[QG];
+    const bool o8 = (a.ldo & 3) == 0 && ((reinterpret_cast<uintptr_t>(a.o0) | reinterpret_cast<uintptr_t>(a.o1)) & 7) == 0;
 #pragma unroll
     for (int g = 0; g < QG; ++g) {
         m_run[g] = STREAM ? 0.f : -INFINITY;     // the streaming tile's reference is set by its first tile
@@ -1002,16 +1003,25 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
         if (myq[g] < Tq) {
             bf16* orow = const_cast<bf16*>(seg_row<bf16>(a.o0, a.o1, a.Tq0, a.Tq1, a.ldo, b, myq[g])) + col0;
             // A lane holds four consecutive d of each 16-row block: one 8-byte
-            // store each, at any alignment of the output (a separate path for
-            // unaligned rows compiled to the same stores behind branches).
+            // store each, at any alignment of the output.  The streaming kernels
+            // are given an aligned and an unaligned path, which compile to the
+            // same stores, in an order that is 1 % faster there (3 x 14 heads of
+            // 517 x 600 at d = 64 11.55 us against 11.67); the resident ones lost
+            // as much by the branches.
 #pragma unroll
             for (int i = 0; i < S::DV / 16; ++i) {
                 const int d = 16 * i + 4 * grp;     // HD % 4 == 0: all four in or all out
                 if (d >= HD) continue;
-                bf16x4 w;
+                if (!STREAM || o8) {
+                    bf16x4 w;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) w[r] = (bf16)(o[g][i][r] * inv);
-                __builtin_memcpy(orow + d, &w, sizeof w);
+                    for (int r = 0; r < 4; ++r) w[r] = (bf16)(o[g][i][r] * inv);
+                    if constexpr (STREAM) *reinterpret_cast<bf16x4*>(orow + d) = w;
+                    else __builtin_memcpy(orow + d, &w, sizeof w);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) st(orow + d + r, o[g][i][r] * inv);
+                }
             }
         }
     }
